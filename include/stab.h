@@ -77,9 +77,8 @@ typedef struct stab_instr {
 typedef struct stab_ctx stab_ctx;
 
 /* Largest qubit count the library supports: 10240 (160 64-bit words of x or z per row; the
- * random-measurement kernel keeps a target's column, 2 * 160 band words, in the registers of
- * one wave, and half a band of the tableau must fit in the 160 KB of LDS of one compute
- * unit). */
+ * planning of random measurements keeps a mask word of every stabilizer row on one compute unit,
+ * and half a band of the tableau must fit in its 160 KB of LDS). */
 int32_t stab_max_qubits(void);
 
 /* Bytes of device memory a context needs in dev_buf for n qubits and `shots` shots in the
@@ -203,13 +202,12 @@ int stab_sample_noalloc(const stab_instr *instrs, int32_t ninstr, const int32_t 
                         void *dev_buf, uint64_t buf_bytes, void *hip_stream, uint8_t *out_bits);
 
 /* Work counters accumulated by a context since creation (for accounting and bandwidth
- * figures): [0] rounds of the random-measurement chain, [1] chain rounds run by a whole block
- * (targets touching many rows), [2] measurements deterministic at layer start, [3] stabilizer
+ * figures): [0] windows of random-at-start targets (up to 256 each), [1] of those, dense ones (a
+ * pivot with x at more than 16 later targets of its window), [2] measurements deterministic at layer start, [3] stabilizer
  * rows multiplied by deterministic reductions, [4] random measurements, [5] stabilizer rows
- * updated by rowsum, [6] measurements found deterministic inside the chain, [7] noise events,
- * [8] destabilizer rows updated by rowsum (replay), [9] destabilizer rows the replay walked,
- * [10] of those, rows it replayed by testing each run target (a pending list overflowed or
- * the lists did not fit), [11] rowsums and replacements in those rows.
+ * updated by rowsum, [6] measurements found deterministic after others of their layer, [7] noise events,
+ * [8] rowsums into destabilizer rows, [9] destabilizer rows changed (once per window), [10] of
+ * those, rows of dense windows, [11] rowsums and replacements in those rows.
  * ncounters <= 12.  Synchronizes the stream. */
 int stab_get_counters(stab_ctx *ctx, uint64_t *counters, int32_t ncounters);
 
@@ -220,9 +218,10 @@ int stab_get_counters(stab_ctx *ctx, uint64_t *counters, int32_t ncounters);
  * stab_get_kernel_times writes, for each kernel id, the summed milliseconds and the number of
  * launches since timing started.  Kernel ids: 0 init, 1 noise draw, 2 segment (gates + noise
  * + column extraction), 3 classes and deterministic outcomes at layer start, 4 outcomes of
- * targets the random chain left deterministic, 5 random chain (stabilizer rows),
- * 6 reset/record, 7 record packing, 8 destabilizer replay, 9 column extraction after a layer
- * with random outcomes.  nkernels <= 10. */
+ * targets that turned deterministic within their layer, 5 planning of a window of
+ * random targets (elimination, snapshots, outcome draws), 6 reset/record, 7 record packing, 8 row
+ * and sign updates of a window of random targets, 9 column extraction after a layer with random
+ * outcomes.  nkernels <= 10. */
 #define STAB_NUM_KERNELS 10
 int stab_set_timing(stab_ctx *ctx, int32_t kernel_mask);
 

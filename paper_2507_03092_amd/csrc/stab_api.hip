@@ -3,8 +3,10 @@
 //
 // Execution order of one stream (the race-safe order of Fig. 2 of the paper): all gates and
 // noise up to a measurement layer run in one segment kernel per 64-row band; a measurement
-// layer then runs classify -> deterministic batch -> in-order random chain -> reset/record.
+// layer then runs classify and deterministic batch -> random targets window by window ->
+// reset/record.
 #include "stab_kernels.hip"
+#include "stab_random.hip"
 #include "stab_batch.hip"
 #include "stab_commute.hip"
 #include "stab.h"
@@ -37,8 +39,6 @@ constexpr int kLdsBytes = 160 * 1024;     // LDS of one gfx950 compute unit
 constexpr int kSegThreads = 1024;
 constexpr int kRedWords = 16;
 constexpr int kMaxShots = 65535;          // grid y dimension of the reset kernel
-constexpr int kReplayThreads = 512;
-constexpr int kReplayStatic = 512;        // bound on k_replay's static LDS
 constexpr int kNumKernels = 10;           // timing ids (include/stab.h)
 
 // 32-bit words of the segment kernel's LDS for one half-band (before the per-shot accumulators)
@@ -49,9 +49,9 @@ int max_qubits_for_lds(int lds_bytes)
     // a staged half-band, 64 * (2*Wc + 1) + kRedWords 32-bit words, must fit
     const int words = lds_bytes / 4 - kRedWords;
     const int wc = (words / 64 - 1) / 2;
-    // register-resident limits: column words per lane (deterministic wave), band words per lane
-    // (chain analysis: 2 * wc <= 64 * kMaxBandsPerLane)
-    return std::min(std::min(wc, 64 * kMaxWordsPerLane), 32 * kMaxBandsPerLane) * 64;
+    // register-resident limits: column words per lane (deterministic wave), stabilizer bands per
+    // thread of k_plan
+    return std::min(std::min(wc, 64 * kMaxWordsPerLane), kMaxBands) * 64;
 }
 
 // STAB_REVERSE_BLOCKS set (and not "0") in the environment: kernels take their workgroups in
@@ -118,9 +118,8 @@ struct stab_ctx {
     size_t arena_cap = 0, arena_used = 0;
     int* d_err = nullptr;
     unsigned long long* d_counters = nullptr;
-    DevBuf xcol, zcol, cls, obuf, events, record, packed, pend;
-    DevBuf plog_p, plog_row, plog_rs, plog_rd, ran;   // pivot log of the random chain
-    DevBuf plist, pcnt, povf;                        // pending targets with x in each pivot
+    DevBuf xcol, zcol, cls, obuf, events, record, packed, pend, ran;
+    DevBuf rnd;                   // scratch of the random measurements (RandBufs)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     // per-kernel timing (stab_set_timing)
     bool timing = false;
@@ -185,11 +184,12 @@ struct stab_program {
     int* d_ev_base = nullptr;
     int* d_ev_count = nullptr;
     long long* d_noise_seg = nullptr;   // per noise instruction: its segment's first event slot
-    int* d_mran = nullptr;              // per measurement layer: a target ran (learning execution)
-    // Per measurement layer, whether a target of it ran in an execution that started from
-    // |0...0> (instruction counter 0).  x|z never depends on outcomes or Pauli noise, so this is
-    // the same in every such execution: later ones skip the chain, the replay, the column
-    // refresh and the second deterministic pass of the layers where nothing ran.
+    int* d_mran = nullptr;              // per measurement layer: its windows of random targets (learning execution)
+    // Per measurement layer, how many windows of random targets it took in an execution that
+    // started from |0...0> (instruction counter 0).  x|z never depends on outcomes or Pauli
+    // noise, so this is the same in every such execution: later ones launch as many windows of
+    // random targets, and skip the column refresh and the second deterministic pass of the layers
+    // that have none.
     std::vector<int> mran;
     bool mran_known = false;
     int* d_mtq = nullptr;
@@ -297,7 +297,7 @@ int tcollect(stab_ctx* ctx)
     return STAB_OK;
 }
 
-// The classify/product pass, the chain and the replay instantiated for the row's words per lane.
+// The classify/product pass instantiated for the row's words per lane.
 using DetFn = decltype(&k_det<1>);
 static DetFn det_kernel(int Wc)
 {
@@ -305,26 +305,67 @@ static DetFn det_kernel(int Wc)
     return wpl <= 1 ? k_det<1> : wpl == 2 ? k_det<2> : wpl == 3 ? k_det<3> : k_det<4>;
 }
 
-using ChainFn = decltype(&k_chain<1>);
-static ChainFn chain_kernel(int Wc)
+// The row updates of a window of random targets for the row's words per lane.
+using ApplyFn = decltype(&k_apply<1>);
+static ApplyFn apply_kernel(int Wc)
 {
     const int wpl = (Wc + 63) / 64;
-    return wpl <= 1 ? k_chain<1> : wpl == 2 ? k_chain<2> : wpl == 3 ? k_chain<3> : k_chain<4>;
+    return wpl <= 1 ? k_apply<1> : wpl == 2 ? k_apply<2> : k_apply<3>;
 }
 
-// The replay instantiated for the row's words per lane.
-using ReplayFn = decltype(&k_replay<1>);
-static ReplayFn replay_kernel(int Wc)
+// Byte offsets of RandBufs' arrays in its buffer, for a program whose largest layer has Kmax
+// targets.
+struct RandLayout {
+    size_t win, piv, cw, dirty, pm, hit, snap, lrd, total;
+    int Tc;
+    bool multi;   // a layer may take more than one window
+};
+
+RandLayout rand_layout(const Geom& g, int Kmax)
 {
-    const int wpl = (Wc + 63) / 64;
-    return wpl <= 1 ? k_replay<1> : wpl == 2 ? k_replay<2> : wpl == 3 ? k_replay<3> : k_replay<4>;
+    RandLayout L{};
+    L.Tc = std::min(64 * kWinChunks, std::max(Kmax, 1));
+    L.multi = Kmax > L.Tc;
+    const size_t ST = (size_t)g.S * L.Tc;
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o += (bytes + 15) & ~(size_t)15;
+        return at;
+    };
+    L.win = take((size_t)g.S * sizeof(int4));
+    L.piv = take(ST * 4);
+    L.cw = take(ST * 4);
+    L.dirty = take(L.multi ? (size_t)g.S * g.NB * 4 : 0);
+    L.pm = take(ST * kWinChunks * 8);
+    L.hit = take(ST * 8);
+    L.snap = take(ST * g.RS * 8);
+    L.lrd = take(ST * (size_t)((g.bpc + 63) / 64) * 8);
+    L.total = o;
+    return L;
 }
 
-#define TIMED(ctx, kind, launch)                 \
+RandBufs rand_bufs(const RandLayout& L, void* p)
+{
+    char* b = (char*)p;
+    RandBufs R{};
+    R.win = (int4*)(b + L.win);
+    R.piv = (int*)(b + L.piv);
+    R.cw = (int*)(b + L.cw);
+    R.dirty = L.multi ? (int*)(b + L.dirty) : nullptr;
+    R.pm = (uint64_t*)(b + L.pm);
+    R.hit = (uint64_t*)(b + L.hit);
+    R.snap = (uint64_t*)(b + L.snap);
+    R.lrd = (uint64_t*)(b + L.lrd);
+    R.Tc = L.Tc;
+    return R;
+}
+
+#define TIMED(ctx, kind, ...)                    \
     do {                                         \
         int rc_ = tstart(ctx, kind);             \
         if (rc_) return rc_;                     \
-        launch;                                  \
+        __VA_ARGS__;                             \
         HIP_CHECK(ctx, hipGetLastError());       \
         rc_ = tstop(ctx, kind);                  \
         if (rc_) return rc_;                     \
@@ -569,18 +610,11 @@ int create_ctx(int32_t n, int32_t shots, int32_t mode, uint64_t seed, uint64_t f
         return fail(STAB_ERANGE, "a half-band of the tableau does not fit in this device's LDS");
     }
     (void)hipFuncSetAttribute((const void*)k_segment, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_chain<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_chain<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_chain<3>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_chain<4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_plan, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
     (void)hipFuncSetAttribute((const void*)k_det<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<3>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_replay<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_replay<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_replay<3>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_replay<4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipGetLastError();
 
     const size_t counter_bytes = kNumCounters * kCounterStripes * sizeof(unsigned long long);
@@ -629,9 +663,7 @@ void stab_destroy(stab_ctx* ctx)
     if (!ctx) return;
     (void)hipStreamSynchronize(ctx->stream);
     DevBuf* bufs[] = {&ctx->xcol, &ctx->zcol, &ctx->cls, &ctx->obuf,
-                      &ctx->events, &ctx->record, &ctx->packed, &ctx->pend, &ctx->plog_p,
-                      &ctx->plog_row, &ctx->plog_rs, &ctx->plog_rd, &ctx->ran, &ctx->plist,
-                      &ctx->pcnt, &ctx->povf};
+                      &ctx->events, &ctx->record, &ctx->packed, &ctx->pend, &ctx->ran, &ctx->rnd};
     for (DevBuf* b : bufs)
         if (b->p && !b->arena) (void)hipFree(b->p);
     if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
@@ -806,8 +838,8 @@ void stab_program_destroy(stab_program* prog)
 namespace {
 
 // Bytes of the device buffers one execution of P needs, in the order xcol, zcol, cls, pend,
-// obuf, events, record, packed, plog_p, plog_rs, plog_row, plog_rd, ran, plist, pcnt, povf.
-constexpr int kExecBufs = 16;
+// obuf, events, record, packed, ran, rnd.
+constexpr int kExecBufs = 10;
 void exec_sizes(const Geom& g, const stab_program& P, bool draw_all, size_t* sizes)
 {
     const size_t K = (size_t)std::max(P.Kmax, 1);
@@ -815,10 +847,8 @@ void exec_sizes(const Geom& g, const stab_program& P, bool draw_all, size_t* siz
     const size_t v[kExecBufs] = {(size_t)g.S * g.NB * K * 8, (size_t)g.S * g.NB * K * 8, (size_t)g.S * K * 4,
                                  (size_t)g.S * K * 4, (size_t)g.B * K,
                                  (size_t)std::max<long long>(draw_all ? P.ev_total : P.ev_cap_max, 1) * 8,
-                                 (size_t)g.B * nrec, (size_t)g.B * ((nrec + 7) / 8), (size_t)g.S * K * 4,
-                                 (size_t)g.S * K * 4, (size_t)g.S * K * g.RS * 8,
-                                 (size_t)g.S * K * ((g.bpc + 63) / 64) * 8, 4, (size_t)g.S * K * kPListCap * 2,
-                                 (size_t)g.S * K * 4, (size_t)g.S * 4};
+                                 (size_t)g.B * nrec, (size_t)g.B * ((nrec + 7) / 8), 4,
+                                 rand_layout(g, P.Kmax).total};
     for (int i = 0; i < kExecBufs; ++i) sizes[i] = v[i];
 }
 
@@ -832,8 +862,7 @@ int exec_prepare(stab_ctx* ctx, const stab_program* P, bool allow_draw_all, bool
     bool draw_all = allow_draw_all && P->nnoise > 0 && P->nnoise <= 65535 && P->ev_total <= kDrawAllEvents;
     int rc;
     DevBuf* bufs[kExecBufs] = {&ctx->xcol, &ctx->zcol, &ctx->cls, &ctx->pend, &ctx->obuf, &ctx->events,
-                               &ctx->record, &ctx->packed, &ctx->plog_p, &ctx->plog_rs, &ctx->plog_row,
-                               &ctx->plog_rd, &ctx->ran, &ctx->plist, &ctx->pcnt, &ctx->povf};
+                               &ctx->record, &ctx->packed, &ctx->ran, &ctx->rnd};
     size_t sizes[kExecBufs];
     exec_sizes(g, *P, draw_all, sizes);
     if (ctx->arena && draw_all) {
@@ -855,41 +884,34 @@ int exec_prepare(stab_ctx* ctx, const stab_program* P, bool allow_draw_all, bool
 // Launch shapes of one execution that depend on the geometry and the device's LDS.
 struct ExecLds {
     int lds_rd = 0;           // per-shot sign accumulators of the segment kernel in LDS
-    size_t seg_lds = 0, chain_lds = 0, replay_lds = 0;
-    int ent_cap = -1;         // replay list entries in LDS (-1: the replay's small form)
+    size_t seg_lds = 0;
 };
 
-int exec_lds(const Geom& g, const stab_program& P, int max_lds, ExecLds* out)
+int exec_lds(const Geom& g, int max_lds, ExecLds* out)
 {
     ExecLds E;
-    const size_t K = (size_t)std::max(P.Kmax, 1);
     // per-shot sign accumulators in LDS only where they keep two half-band blocks per compute
     // unit (or where even one block without them would not get two)
     const int seg_base = seg_lds_words(g.RS) * 4, seg_acc = (seg_lds_words(g.RS) + g.bpc) * 4;
     E.lds_rd = (seg_acc <= max_lds / 2 || (seg_base > max_lds / 2 && seg_acc <= max_lds)) ? 1 : 0;
     E.seg_lds = (size_t)(seg_lds_words(g.RS) + (E.lds_rd ? g.bpc : 0)) * 4;
-    E.chain_lds = (size_t)chain_lds_layout(g).total;
-    if (E.chain_lds + kReplayStatic > (size_t)max_lds)   // (a bound on its static LDS too)
-        return fail(STAB_ERANGE, "too many shots per copy for the chain kernel");
-    // the replay's list form when its fixed part leaves room for list entries in LDS
-    const ReplayLds RL = replay_lds_layout((int)K, (g.bpc + 63) / 64, kReplayThreads / 64);
-    // (kReplayStatic bytes of the block's LDS are its own __shared__ variables)
-    E.replay_lds = (size_t)RL.small_bytes;
-    const int replay_room = max_lds - kReplayStatic;
-    if (replay_walk_fits((int)K) && RL.fixed_bytes + 2 * 1024 <= replay_room) {
-        E.ent_cap = std::min((replay_room - RL.fixed_bytes) / 2, (int)K * kPListCap);
-        E.replay_lds = (size_t)RL.fixed_bytes + 2 * (size_t)E.ent_cap;
-    }
-    if (E.replay_lds > (size_t)replay_room) return fail(STAB_ERANGE, "too many shots per copy for the replay kernel");
     *out = E;
     return STAB_OK;
 }
 
 // Every launch of one execution of P on ctx->stream, eagerly or into a graph (a fill kernel
 // clears the event counts: no memset node in a captured graph).  use_mran skips the launches of
-// measurement layers where nothing ran in an earlier execution from |0...0>; learn_mran marks,
-// in P->d_mran, the layers where something runs.
-int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, bool learn_mran)
+// measurement layers where nothing ran in an earlier execution from |0...0>; learn_mran writes,
+// in P->d_mran, how many windows of random targets each layer took.  may_sync: the caller allows
+// waiting for the stream (not while capturing, nor in the server).
+// targets of a window (one word of shots) up to which k_plan's waves take the snapshots, two each,
+// which saves a launch
+constexpr int kFusedSnaps = 32;
+// windows launched without knowing the pending targets (waiting for the count costs about as much
+// as ten launches that return at once)
+constexpr int kMaxBlindWindows = 4;
+
+int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, bool learn_mran, bool may_sync)
 {
     const Geom& g = ctx->g;
     uint64_t* Xcol = (uint64_t*)ctx->xcol.p;
@@ -901,15 +923,17 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
     const uint64_t base = ctx->instr_counter;
 
     ExecLds E;
-    int rc = exec_lds(g, *P, ctx->max_lds, &E);
+    int rc = exec_lds(g, ctx->max_lds, &E);
     if (rc) return rc;
-    const int lds_rd = E.lds_rd, ent_cap = E.ent_cap;
-    const size_t seg_lds = E.seg_lds, chain_lds = E.chain_lds, replay_lds = E.replay_lds;
-    int* plog_p = (int*)ctx->plog_p.p;
-    int* plog_rs = (int*)ctx->plog_rs.p;
-    uint64_t* plog_row = (uint64_t*)ctx->plog_row.p;
-    uint64_t* plog_rd = (uint64_t*)ctx->plog_rd.p;
+    const int lds_rd = E.lds_rd;
+    const size_t seg_lds = E.seg_lds;
     int* ran = (int*)ctx->ran.p;
+    const RandLayout RL = rand_layout(g, P->Kmax);
+    const RandBufs R = rand_bufs(RL, ctx->rnd.p);
+    const bool wide = g.NR > kPlanRows;
+    const int plan_threads = 64 * std::min(16, g.Wr), plan_lds = plan_lds_bytes(g.NR);
+    const int aw = (g.Wc + 63) / 64;                      // k_apply's words per lane
+    const int apply_thr = apply_threads(aw);
 
     const long long nbytes = (P->nrec + 7) / 8;
     if (P->nnoise > 0)
@@ -964,20 +988,36 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
             const size_t det_lds = (size_t)dt * (g.NB + (g.bpc + 63) / 64) * 8;
             TIMED(ctx, 3, (det_kernel(g.Wc)<<<dgrid, 64 * dt, det_lds, ctx->stream>>>(g, ctx->tab, ctx->rs, ctx->rd, Xcol, K2, cls,
                                                                        obuf, ran, ctx->d_err, ctx->d_counters, 0, nullptr)));
-            // a layer where nothing ran in an earlier execution from |0...0>: the next four
-            // launches would return at once
-            if (!use_mran || P->mran[st.second]) {
-            TIMED(ctx, 5, (chain_kernel(g.Wc)<<<g.S, chain_threads((g.Wc + 63) / 64), chain_lds, ctx->stream>>>(
-                              g, ctx->tab, ctx->rs, ctx->rd, Xcol, Zcol, K2, cls, P->d_mtq + m.tq_begin,
-                              (int*)ctx->pend.p, ctx->seed, ctx->first_shot, base + m.instr,
-                              m.pos_base, plog_p, plog_row, plog_rs, plog_rd, ran, (uint16_t*)ctx->plist.p,
-                              (int*)ctx->pcnt.p, (int*)ctx->povf.p, obuf, ctx->d_err, ctx->d_counters)));
-            // destabilizer updates of the run targets, then fresh columns of the final tableau
-            // (skipped on the device when nothing ran)
-            TIMED(ctx, 8, (replay_kernel(g.Wc)<<<dim3(g.Wr, g.S), kReplayThreads, replay_lds, ctx->stream>>>(
-                              g, ctx->tab, ctx->rs, ctx->rd, Xcol, K2, P->d_mtq + m.tq_begin, plog_p, plog_row,
-                              plog_rs, plog_rd, (const uint16_t*)ctx->plist.p, (const int*)ctx->pcnt.p,
-                              (const int*)ctx->povf.p, ran, ent_cap, ctx->d_err, ctx->d_counters)));
+            // a layer where nothing ran in an earlier execution from |0...0>: the next launches
+            // would return at once; otherwise that execution's count of windows is known
+            const int known = use_mran ? P->mran[st.second] : -1;
+            if (known != 0) {
+            // (above n = 4096 a window can be cut to 64 targets)
+            int nwin = known > 0 ? known : (K2 + (wide ? 64 : R.Tc) - 1) / (wide ? std::min(64, R.Tc) : R.Tc);
+            const bool ask = known < 0 && may_sync && nwin > kMaxBlindWindows;
+            int until = ask ? 1 : nwin;
+            const Snap snap{ctx->tab, ctx->rs, ctx->rd, obuf, ctx->seed, ctx->first_shot, base + m.instr, m.pos_base,
+                            g.bpc <= 64 && std::min(R.Tc, K2) <= kFusedSnaps};
+            for (int w = 0; w < nwin; ++w) {
+                if (w == until) {
+                    // many windows that may all be empty: read how many targets are left
+                    int v[4] = {0, 0, 0, 0};   // the first copy's (the same in all)
+                    HIP_CHECK(ctx, hipMemcpyAsync(v, R.win, 16, hipMemcpyDeviceToHost, ctx->stream));
+                    HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
+                    const int left = v[0] - v[1] - (v[2] & ~kDenseFlag);
+                    if (left <= 0) break;
+                    until = w + (left + R.Tc - 1) / R.Tc;
+                }
+                TIMED(ctx, 5, {
+                    k_plan<<<g.S, plan_threads, plan_lds, ctx->stream>>>(g, Xcol, K2, cls, (int*)ctx->pend.p, R, w,
+                                                                         ran, snap, ctx->d_counters);
+                    if (!snap.fused)
+                        k_snap<<<dim3(R.Tc, g.S), kSnapThreads, 0, ctx->stream>>>(g, K2, (const int*)ctx->pend.p, snap, R);
+                });
+                TIMED(ctx, 8, (apply_kernel(g.Wc)<<<dim3(8 * g.Wr, g.S), apply_thr, 0, ctx->stream>>>(
+                                  g, ctx->tab, ctx->rs, ctx->rd, Xcol, K2, P->d_mtq + m.tq_begin,
+                                  (const int*)ctx->pend.p, R, obuf, ctx->d_err, ctx->d_counters)));
+            }
             {
                 SegArgs a{};
                 a.items = P->d_items;
@@ -996,7 +1036,7 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
                 TIMED(ctx, 9, (k_segment<<<dim3(2 * g.NB, g.S), kSegThreads, (size_t)seg_lds_words(g.RS) * 4,
                                            ctx->stream>>>(g, ctx->tab, ctx->rs, ctx->rd, a)));
             }
-            // targets the chain found deterministic: reduced in parallel on the final tableau
+            // targets found deterministic within the layer: reduced in parallel on the final tableau
             TIMED(ctx, 4, (det_kernel(g.Wc)<<<dgrid, 64 * dt, det_lds, ctx->stream>>>(g, ctx->tab, ctx->rs, ctx->rd, Xcol, K2, cls,
                                                                        obuf, ran, ctx->d_err, ctx->d_counters, 1,
                                                                        learn_mran ? P->d_mran + st.second : nullptr)));
@@ -1037,7 +1077,9 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
     const uint64_t base = ctx->instr_counter;
     const bool use_mran = base == 0 && P->mran_known;
     const bool learn_mran = base == 0 && !P->mran_known && !P->meas.empty();
-    auto enqueue = [&]() -> int { return exec_enqueue(ctx, P, draw_all, use_mran, learn_mran); };
+    auto enqueue = [&](bool may_sync) -> int {
+        return exec_enqueue(ctx, P, draw_all, use_mran, learn_mran, may_sync);
+    };
 
     if (ctx->ev0) HIP_CHECK(ctx, hipEventRecord(ctx->ev0, ctx->stream));
     if (ctx->graph_on && !ctx->timing && !learn_mran) {
@@ -1045,8 +1087,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
         // buffers: replay the captured graph while they are unchanged, capture again otherwise
         uint64_t bufsig = 0;
         const DevBuf* bufs[] = {&ctx->xcol, &ctx->zcol, &ctx->cls, &ctx->obuf, &ctx->events, &ctx->record,
-                                &ctx->packed, &ctx->pend, &ctx->plog_p, &ctx->plog_row, &ctx->plog_rs,
-                                &ctx->plog_rd, &ctx->ran, &ctx->plist, &ctx->pcnt, &ctx->povf};
+                                &ctx->packed, &ctx->pend, &ctx->ran, &ctx->rnd};
         for (const DevBuf* b : bufs) bufsig = bufsig * 1099511628211ull ^ (uint64_t)(uintptr_t)b->p;
         const uint64_t key[5] = {P->serial, ctx->seed, ctx->first_shot, base, bufsig};
         if (!ctx->gexec || std::memcmp(key, ctx->gkey, sizeof(key)) != 0) {
@@ -1058,7 +1099,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
             HIP_CHECK(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
             hipStream_t run_stream = ctx->stream;
             ctx->stream = ctx->cap_stream;          // the launches below are recorded, not run
-            const int erc = enqueue();
+            const int erc = enqueue(false);
             hipGraph_t gr = nullptr;
             const hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &gr);
             ctx->stream = run_stream;
@@ -1072,7 +1113,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
             std::memcpy(ctx->gkey, key, sizeof(key));
         }
         HIP_CHECK(ctx, hipGraphLaunch(ctx->gexec, ctx->stream));
-    } else if ((rc = enqueue())) {
+    } else if ((rc = enqueue(true))) {
         return rc;
     }
     std::vector<uint8_t> host;
@@ -1230,7 +1271,7 @@ int stab_sample(const stab_instr* instrs, int32_t ninstr, const int32_t* targets
 // once per device with hipGetSymbolAddress and only that address is handed to kernels and
 // copies.  Calls on one GPU share the array, so calls that overlap on one GPU race.
 // ---------------------------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[STAB_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[STAB_NOALLOC_SCRATCH_BYTES + (8 << 20)];
 
 namespace {
 
@@ -1257,8 +1298,13 @@ int scratch_address(char** out)
     return STAB_OK;
 }
 
-// Scratch bytes stab_sample_noalloc carves for this program (noise drawn segment by segment),
-// in the order the context takes them.
+// Scratch bytes stab_sample_noalloc counts against its limit for this program (noise drawn
+// segment by segment).  The random measurements are counted per target of the largest layer (44
+// bytes, a row and its per-shot signs, seven pieces), which bounds what a window of them takes
+// (rand_layout: 48 bytes, a row and signs for at most 64 kWinChunks targets, 16 bytes a copy) to
+// within kScratchSlack.
+constexpr size_t kScratchSlack = 8 << 20;
+
 size_t noalloc_bytes(const Geom& g, const stab_program& P, size_t blob_bytes)
 {
     auto piece = [](size_t b) { return std::max<size_t>(align256(b), 256); };
@@ -1266,7 +1312,10 @@ size_t noalloc_bytes(const Geom& g, const stab_program& P, size_t blob_bytes)
                    piece(blob_bytes);
     size_t sizes[kExecBufs];
     exec_sizes(g, P, false, sizes);
-    for (size_t b : sizes) total += piece(b);
+    for (int i = 0; i < kExecBufs - 1; ++i) total += piece(sizes[i]);
+    const size_t SK = (size_t)g.S * (size_t)std::max(P.Kmax, 1);
+    total += 3 * piece(SK * 4) + piece(SK * g.RS * 8) + piece(SK * (size_t)((g.bpc + 63) / 64) * 8) +
+             piece(SK * 2 * kListCap) + piece((size_t)g.S * 4);
     return total;
 }
 
@@ -1297,7 +1346,7 @@ extern "C" int stab_sample_noalloc(const stab_instr* instrs, int32_t ninstr, con
     if ((rc = scratch_address(&arena))) return rc;
     stab_ctx* ctx = nullptr;
     if ((rc = create_ctx(n, shots, mode, seed, 0, dev_buf, buf_bytes, hip_stream, arena,
-                         (size_t)STAB_NOALLOC_SCRATCH_BYTES, &ctx)))
+                         (size_t)STAB_NOALLOC_SCRATCH_BYTES + kScratchSlack, &ctx)))
         return rc;
     rc = upload_program(ctx, P, B);
     if (rc == STAB_OK) rc = stab_execute(ctx, &P, out_bits, nullptr);

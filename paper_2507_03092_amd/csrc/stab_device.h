@@ -7,9 +7,8 @@ namespace stabdev {
 
 // Most 64-bit column words a lane of the deterministic-measurement wave keeps in registers.
 constexpr int kMaxWordsPerLane = 4;
-// Most sign/band words (2 * ceil(n/64)) a lane of the chain's analysis wave reads.
-constexpr int kMaxBandsPerLane = 5;
-constexpr int kMaxStabBandsPerLane = (32 * kMaxBandsPerLane + 63) / 64;   // the stabilizer half
+// Most 64-row bands of a half: the stabilizer rows k_plan keeps in registers (16 waves of 10).
+constexpr int kMaxBands = 160;
 
 struct Geom {
     int n;    // qubits
@@ -47,46 +46,6 @@ constexpr int kNumCounters = 12;
 __device__ __forceinline__ void count_add(unsigned long long* counters, int idx, unsigned long long v)
 {
     if (counters) atomicAdd(&counters[idx * kCounterStripes + (blockIdx.x & (kCounterStripes - 1))], v);
-}
-
-// Random-measurement chain: window of pending targets, rows a batched target may touch, and
-// the largest batch whose pivot rows are staged in LDS so all waves share its rowsums.
-constexpr int kWin = 64;
-constexpr int kRCap = 128;
-constexpr int kWide = 4;
-constexpr int kAnalyze = 48;     // window entries (re)analysed per round, at most
-constexpr int kAffCap = 1024;    // column-upkeep work list of a wide batch
-constexpr int kPListCap = 16;    // pending targets listed per run target (more: replay walks rows)
-
-// Dynamic LDS layout of the chain kernel (byte offsets), shared by host and device.
-struct ChainLds {
-    int solo;    // block-solo buffers: 2 rows, 2 band masks, per-shot pivot signs, word list
-    int owner;   // NR ints: first window target owning each row pair
-    int wide;    // kWide pivot rows of the batch
-    int words;   // kWide x kRCap (word, mask) lists of the batch's rowsum rows
-    int aff;     // kAffCap column-upkeep entries {code, flags, batch index}
-    int win;     // window arrays: 9 x kWin ints + kWin x kRCap row indices
-    int tm;      // n int16: qubit -> pending target whose x column is kept, or -1
-    int pbit;    // NR bits: row pairs that are pivots of the round's executed targets
-    int total;
-};
-
-__host__ __device__ inline int align16i(int v) { return (v + 15) & ~15; }
-
-__host__ __device__ inline ChainLds chain_lds_layout(const Geom& g)
-{
-    ChainLds L;
-    const int nrdw = (g.bpc + 63) / 64;
-    L.solo = 0;
-    L.owner = align16i((2 * g.RS + 2 * g.NB + nrdw) * 8 + g.NB * 4);
-    L.wide = L.owner + align16i(g.NR * 4);
-    L.words = L.wide + kWide * g.RS * 8;
-    L.aff = L.words + kWide * kRCap * 12;
-    L.win = L.aff + kAffCap * 12;
-    L.tm = L.win + (9 * kWin + kWin * kRCap) * 4;
-    L.pbit = L.tm + align16i(g.n * 2);
-    L.total = L.pbit + align16i((g.NR + 31) / 32 * 4);
-    return L;
 }
 
 struct SegArgs {

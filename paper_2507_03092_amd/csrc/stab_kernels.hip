@@ -168,54 +168,27 @@ __device__ __forceinline__ int wave_sum_uniform(int v, int lane)
     return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 32);
 }
 
-// Sorted rows as (64-row word, bit mask) runs.  rows[64 h + lane] belongs to lane `lane` of half
-// h (nrows <= 128); a lane heads a run when its row starts a new word or the half, so one word
-// may head a run in both halves, with disjoint masks.  hm[h]: the head lanes; the head's wv[h]
-// and mv[h] are its run's word and mask (a segmented OR over the run's lanes).  Whole wave.
-__device__ __forceinline__ void row_runs(const int* rows, int nrows, int lane, uint64_t* hm, int* wv, uint64_t* mv)
+__device__ __forceinline__ int wave_min(int v)
 {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        hm[h] = 0ull;
-        wv[h] = 0;
-        mv[h] = 0ull;
-        const int nv = min(nrows - 64 * h, 64);
-        if (nv <= 0) continue;
-        const int r = 64 * h + lane;
-        const bool valid = lane < nv;
-        const int row = valid ? rows[r] : 0;
-        const int w = row >> 6;
-        const bool head = valid && (lane == 0 || (rows[r - 1] >> 6) != w);
-        const uint64_t H = __ballot(head);
-        const uint64_t after = lane < 63 ? H >> (lane + 1) : 0ull;
-        const int end = after ? lane + 1 + ctz64(after) : nv;
-        uint64_t acc = valid ? 1ull << (row & 63) : 0ull;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint64_t v = shfl_u64(acc, lane + off < 64 ? lane + off : lane);
-            if (lane + off < end) acc |= v;
-        }
-        hm[h] = H;
-        wv[h] = w;
-        mv[h] = acc;
-    }
+    for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m, 64));
+    return v;
 }
 
-// f(word, mask) for every run of row_runs, in a scalar loop over the head lanes (the words and
-// masks are read out of their lanes whatever the exec mask, so f may run under a lane mask).
-template <class F>
-__device__ __forceinline__ void for_runs(const uint64_t* hm, const int* wv, const uint64_t* mv, F f)
+__device__ __forceinline__ int wave_excl_scan(int v, int lane)
 {
+    int incl = v;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint64_t H = hm[h];
-        while (H) {
-            const int l = ctz64(H);
-            H &= H - 1;
-            f(__builtin_amdgcn_readlane(wv[h], l), readlane_u64(mv[h], l));
-        }
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += o;
     }
+    return incl - v;
 }
+
+// v is the same in every lane (the compiler cannot see that for values read from LDS): keeping
+// it in a scalar register makes loops over it scalar loops.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // ------------------------------------------------------------------------------------------
 // init: |0...0> -- destabilizer i = +X_i, stabilizer i = +Z_i, all signs 0.
@@ -578,10 +551,10 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
 // pass 0, at layer start: the block's eight consecutive targets have their x columns staged in
 // LDS first (a band's eight words are contiguous in Xcol, so the loads are coalesced), then a
 // wave takes each target's column one word per 64-row band and lane.  The first stabilizer with x at the qubit is the pivot: the target is
-// random, its class is that stabilizer index (the random chain takes it).  Without one the
+// random, its class is that stabilizer index (k_plan and k_apply take it).  Without one the
 // outcome is deterministic: +-Z_a is the product of the stabilizers NR + i over the
-// destabilizers i with x at the qubit (class -1).  pass 1, after the chain on the final
-// tableau (only when a random target ran): the targets the chain marked deterministic (-2)
+// destabilizers i with x at the qubit (class -1).  pass 1, after the random targets on the final
+// tableau (only when one ran): the targets k_plan marked deterministic (-2)
 // are reduced and marked -3.  A deterministic outcome is unchanged by Z measurements and
 // resets on other qubits, so every one of a layer is reduced in parallel (the paper
 // serialises every row behind two grid barriers, Alg. 2).
@@ -623,7 +596,7 @@ k_det(Geom g, const uint64_t* __restrict__ tab, const uint64_t* __restrict__ rs,
         s_rows = 0;
     }
     if (pass == 0) {
-        // the next launch (the random chain) sets this when a random target runs
+        // the next launch (k_plan) sets this when a random target runs
         if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ran = 0;
     } else {
         // (ran_log, when given: whether a target of this layer ran, for the host)
@@ -794,1406 +767,6 @@ k_det(Geom g, const uint64_t* __restrict__ tab, const uint64_t* __restrict__ rs,
     if (threadIdx.x == 0 && s_det) {
         count_add(counters, pass == 0 ? 2 : 6, (unsigned long long)s_det);
         count_add(counters, 3, (unsigned long long)s_rows);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// Random-at-start targets of a measurement layer, one block per tableau copy.
-//
-// Sequential semantics (Sec. 2.4): targets are measured in op order; each may have turned
-// deterministic because of an earlier one in the same layer.  A random one: pivot p = first
-// stabilizer with x at the qubit; rowsum(i, p) for every other row i with x at the qubit; the
-// pivot's destabilizer q <- old row p (its own rowsum is overwritten); p <- Z_a with the
-// outcome as sign.  A deterministic one reads the stabilizers selected by the destabilizers
-// with x at the qubit.
-//
-// Split of the work.  Nothing a later target of the layer decides on (its pivot, its row
-// list, its outcome) depends on destabilizer rows, so this kernel runs the stabilizer half
-// only and logs each executed target's old pivot row with its signs; k_replay then applies
-// the destabilizer updates (rowsums and the q <- p moves) in op order, one wave per touched
-// destabilizer, all rows in parallel.  Targets that turn deterministic are marked and
-// reduced after the layer on the final tableau.
-//
-// Batching: the block looks at a window of the next pending targets.  A target's stabilizer
-// rows are its pivot and the other stabilizers with x at its qubit.  Target t of the window
-// runs now iff none of its stabilizer rows belongs to an earlier window target (run or
-// deferred).  Such targets touch disjoint rows, and every later target whose inputs an
-// earlier one could change shares a row with it (the earlier pivot would have x at the later
-// qubit), so running them at once gives exactly the sequential result; shared words (signs,
-// target columns) are updated with XOR, AND and OR atomics on distinct bits.  A target
-// touching more than kRCap rows runs alone, with the whole block.  The stabilizer half of
-// Xcol is kept equal to the current tableau's x columns of the pending targets; the whole of
-// Xcol/Zcol is extracted again after the replay.
-// ------------------------------------------------------------------------------------------
-enum { T_RANDOM = 0, T_DET = 1, T_BIG_RANDOM = 2, T_BIG_DET = 3, T_UNKNOWN = 4, T_DEAD = 5 };
-
-__device__ __forceinline__ int wave_min(int v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m, 64));
-    return v;
-}
-
-__device__ __forceinline__ int wave_excl_scan(int v, int lane)
-{
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
-    return incl - v;
-}
-
-struct ChainCtx {
-    Geom g;
-    uint64_t* tb;        // this copy's tableau
-    uint64_t* rs;        // this copy's sign words
-    uint64_t* rd;        // all shots' sign words
-    uint64_t* X;         // this copy's Xcol
-    uint64_t* Z;
-    int K, s;
-    const int* tq;
-    int16_t* tm;             // (LDS) qubit -> pending target whose x column is kept, or -1
-    int* cl;                 // this copy's target classes (-2 marks "deterministic now")
-    int* lp;                 // pivot log: stabilizer index of target k's pivot (-1: not run)
-    uint64_t* lrow;          // old pivot row of target k (RS words)
-    int* lrs;                // its shared sign
-    uint64_t* lrd;           // its per-shot signs (nrdw words, bit b = shot b of the copy)
-    int nrdw;
-    int* ran;                // set to 1 when any random target of the layer runs
-    uint16_t* plist;         // per run target k: pending targets whose qubit has x in its pivot
-    int* pcnt;               // their count (kPListCap at most; *povf = 1 beyond)
-    int* povf;
-    uint64_t seed, first_shot, instr;
-    int pos_base;
-    uint8_t* obuf;
-    int* err;
-    unsigned long long* counters;
-    unsigned int* lcnt;      // (LDS) random measurements and stabilizer rows updated, flushed at the end
-};
-
-// Pending target k2 has x in the pivot row of target k: the replay must flip that bit of a
-// destabilizer it multiplies by the pivot.
-__device__ __forceinline__ void plist_add(const ChainCtx& c, int k, int k2)
-{
-    const int slot = atomicAdd(&c.pcnt[k], 1);
-    if (slot < kPListCap) c.plist[(size_t)k * kPListCap + slot] = (uint16_t)k2;
-    else *c.povf = 1;
-}
-
-// Outcome draw of target k for global shot index b.
-__device__ __forceinline__ int outcome_bit(const ChainCtx& c, int k, int b)
-{
-    uint64_t u0, u1;
-    philox(c.instr, (uint64_t)(c.pos_base + k), c.seed, c.first_shot + (uint64_t)b, u0, u1);
-    return (int)(u0 >> 63);
-}
-
-// v is the same in every lane (the compiler cannot see that for values read from LDS): keeping
-// it in a scalar register makes loops over it scalar loops.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// An empty asm that takes v in a VGPR and may change it: the compiler waits for v's load here
-// (not at a later first use that some paths skip) and keeps work that uses v below this point.
-__device__ __forceinline__ void settle(uint64_t& v) { asm volatile("" : "+v"(v)); }
-
-// rowsum(i, p) for rows[r], r = r0, r0 + stride, ... < nrows, pivot row words in registers
-// (lane owns column words lane + 64 t, WPL = ceil(Wc / 64)).  Sign r_i <- r_i ^ r_p ^
-// (i-power / 2).  Every batch loads RB rows (the last row again past nrows, a stabilizer row
-// when there is none) and settles every loaded word, so the number of loads in flight never
-// depends on the path taken and no load is left pending for a later loop to wait on: the
-// first batch's loads are issued before anything waits for the pivot row, whose loads (and the
-// caller's pend[] words, loaded before it) are settled right after.  r_p = bit rbit of pend[0].
-template <int WPL, int NP>
-__device__ __forceinline__ void rowsum_rows(const ChainCtx& c, uint64_t* xp, uint64_t* zp, uint64_t (&pend)[NP],
-                                            int rbit, const int* rows, int nrows, int r0, int stride, int lane)
-{
-    const Geom& g = c.g;
-    const int Wc = g.Wc, RS = g.RS;
-    nrows = uni(nrows);
-    r0 = uni(r0);
-    stride = uni(stride);
-    rbit = uni(rbit);
-    // rows in flight: four, three when a lane holds three or more words of a row
-    constexpr int RB = WPL <= 2 ? 4 : 3;
-    uint64_t rx[RB][WPL], rz[RB][WPL];
-    auto row_of = [&](int r) { return nrows > 0 ? rows[min(r, nrows - 1)] : g.NR; };
-    auto load = [&](int rb) {
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const uint64_t* row = c.tb + (size_t)row_of(rb + u * stride) * RS;
-#pragma unroll
-            for (int t = 0; t < WPL; ++t) {
-                // (lanes past Wc read the last word and hold a zero pivot word)
-                const int cw = min(lane + 64 * t, Wc - 1);
-                rx[u][t] = row[cw];
-                rz[u][t] = row[Wc + cw];
-            }
-        }
-    };
-    load(r0);
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        settle(xp[t]);
-        settle(zp[t]);
-    }
-#pragma unroll
-    for (int i = 0; i < NP; ++i) settle(pend[i]);
-    const int rsp = (int)((pend[0] >> rbit) & 1ull);
-    for (int rb = r0;;) {
-        // the batch's words are taken here, whether or not a row is past nrows
-#pragma unroll
-        for (int u = 0; u < RB; ++u)
-#pragma unroll
-            for (int t = 0; t < WPL; ++t) {
-                settle(rx[u][t]);
-                settle(rz[u][t]);
-            }
-        // only the i-power mod 4 matters: byte u of P sums row u's per-lane residues (at most
-        // 64 x 3), so one wave sum serves the batch
-        int P = 0;
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const int r = rb + u * stride;
-            int G = 0;
-#pragma unroll
-            for (int t = 0; t < WPL; ++t) G += gsum(xp[t], zp[t], rx[u][t], rz[u][t]);
-            if (r < nrows) {
-                uint64_t* row = c.tb + (size_t)rows[r] * RS;
-#pragma unroll
-                for (int t = 0; t < WPL; ++t) {
-                    const int cw = lane + 64 * t;
-                    if (cw < Wc && (xp[t] | zp[t])) {
-                        row[cw] = rx[u][t] ^ xp[t];
-                        row[Wc + cw] = rz[u][t] ^ zp[t];
-                    }
-                }
-                P |= (G & 3) << (8 * u);
-            }
-        }
-        P = wave_sum_uniform(P, lane);
-        if (lane == 0) {
-#pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                const int r = rb + u * stride;
-                if (r < nrows) {
-                    const int G = (P >> (8 * u)) & 3;
-                    const int i = rows[r];
-                    if (G & 1) atomicOr(c.err, 4);
-                    const uint64_t flip = (uint64_t)((rsp ^ (G >> 1)) & 1) << (i & 63);
-                    if (flip) atomicXor((unsigned long long*)&c.rs[i >> 6], (unsigned long long)flip);
-                }
-            }
-        }
-        rb += RB * stride;
-        if (rb >= nrows) break;
-        load(rb);
-    }
-}
-
-// The rest of a random measurement, one wave: per-shot signs of the rowsum rows and the
-// outcomes, the pending targets' x columns at the rowsum rows and at p, the pivot log entry
-// (old row p with its signs, for the destabilizer replay) and p <- Z_a.  xp, zp: the old row p
-// (lane owns column words lane + 64 t).  rows[] (stabilizer rows) is sorted, so runs in one
-// 64-row word are applied as one word mask.  Column upkeep follows tmap (k >= 0: the pending
-// target whose x column is kept).  When `aff` is given (wide batches), the per-target column
-// work is appended there as {target, 0, batch index j} for the whole block to apply; it is
-// done in-wave otherwise or when the list is full.
-template <int WPL>
-__device__ void random_epilogue(const ChainCtx& c, int k, int a, int ip, int rsp, const uint64_t* xp,
-                                const uint64_t* zp, const int* rows, int nrows, int lane,
-                                int* aff = nullptr, int* aff_n = nullptr, int j = 0,
-                                bool have_rd0 = false, uint64_t rd0 = 0, uint64_t rd1 = 0,
-                                int out0 = 0, int out1 = 0)
-{
-    const Geom& g = c.g;
-    const int Wc = g.Wc, Wr = g.Wr, NB = g.NB, RS = g.RS, K = c.K;
-    k = uni(k);
-    a = uni(a);
-    ip = uni(ip);
-    rsp = uni(rsp);
-    nrows = uni(nrows);
-    j = uni(j);
-    uint64_t* gp = c.tb + (size_t)(g.NR + ip) * RS;
-    const int wq = ip >> 6;
-    const uint64_t bq = 1ull << (ip & 63);
-    uint64_t* lrow = c.lrow + (size_t)k * RS;
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        const int cw = lane + 64 * t;
-        if (cw < Wc) {
-            lrow[cw] = xp[t];
-            lrow[Wc + cw] = zp[t];
-        }
-    }
-    if (lane == 0) {
-        c.lrs[k] = rsp;
-        c.lp[k] = ip;
-        *c.ran = 1;
-        atomicAnd((unsigned long long*)&c.rs[Wr + wq], ~(unsigned long long)bq);
-    }
-    // the rowsum rows as word runs, read out as scalars by every loop below
-    uint64_t hm[2], mv[2];
-    int wv[2];
-    row_runs(rows, nrows, lane, hm, wv, mv);
-    // 64 shots: rw = each shot's pivot sign word, out = its outcome draw
-    auto shots = [&](int b0, uint64_t rw, int out) {
-        const int b = b0 + lane;
-        const bool in = b < g.bpc;
-        const int gb = c.s * g.bpc + min(b, g.bpc - 1);
-        uint64_t* rdb = c.rd + (size_t)gb * NB;
-        const bool rdp = in && ((rw >> (ip & 63)) & 1ull) != 0;
-        if (in) {
-            // the pivot's sign becomes the outcome (no rowsum row is the pivot)
-            if ((int)rdp != out) atomicXor((unsigned long long*)&rdb[Wr + wq], (unsigned long long)bq);
-            c.obuf[(size_t)gb * K + k] = (uint8_t)out;
-        }
-        for_runs(hm, wv, mv, [&](int w, uint64_t m) {
-            if (rdp) atomicXor((unsigned long long*)&rdb[w], (unsigned long long)m);
-        });
-        const uint64_t m = __ballot(rdp);
-        if (lane == 0) c.lrd[(size_t)k * c.nrdw + (b0 >> 6)] = m;
-    };
-    int b0 = 0;
-    if (have_rd0) {
-        // the first 128 shots' sign words and draws came with the pivot row: no load waits here
-        shots(0, rd0, out0);
-        if (g.bpc > 64) shots(64, rd1, out1);
-        b0 = 128;
-    }
-    for (; b0 < g.bpc; b0 += 64) {
-        const int gb = c.s * g.bpc + min(b0 + lane, g.bpc - 1);
-        shots(b0, c.rd[(size_t)gb * NB + Wr + wq], outcome_bit(c, k, gb));
-    }
-    // x columns of pending targets: rows with x at the pivot's qubits flip there; p's x clears
-    auto upkeep = [&](int k2) {
-        unsigned long long* X2 = (unsigned long long*)(c.X + k2);
-        for_runs(hm, wv, mv, [&](int w, uint64_t m) { atomicXor(&X2[(size_t)w * K], (unsigned long long)m); });
-        atomicAnd(&X2[(size_t)(Wr + wq) * K], ~(unsigned long long)bq);
-    };
-    if (aff) {
-#pragma unroll
-        for (int t = 0; t < WPL; ++t) {
-            const int cw = lane + 64 * t;
-            if (cw >= Wc) continue;
-            uint64_t bits = xp[t];
-            while (bits) {
-                const int bit = ctz64(bits);
-                bits &= bits - 1;
-                const int k2 = c.tm[cw * 64 + bit];
-                if (k2 < 0 || k2 == k) continue;
-                const int slot = atomicAdd(aff_n, 1);
-                if (slot < kAffCap) {
-                    aff[3 * slot] = k2;
-                    aff[3 * slot + 1] = 0;
-                    aff[3 * slot + 2] = j;
-                    continue;
-                }
-                plist_add(c, k, k2);
-                upkeep(k2);
-            }
-        }
-    } else {
-        // this wave is the only writer of target k's list: slots by ballot rank, no atomics
-        int np = 0;
-#pragma unroll
-        for (int t = 0; t < WPL; ++t) {
-            const int cw = lane + 64 * t;
-            uint64_t bits = cw < Wc ? xp[t] : 0ull;
-            while (__ballot(bits != 0ull)) {
-                int k2 = -1;
-                if (bits) {
-                    const int bit = ctz64(bits);
-                    bits &= bits - 1;
-                    k2 = c.tm[cw * 64 + bit];
-                }
-                const bool hit = k2 >= 0 && k2 != k;
-                const uint64_t hm = __ballot(hit);
-                if (hit) {
-                    const int slot = np + __popcll(hm & ((1ull << lane) - 1ull));
-                    if (slot < kPListCap) c.plist[(size_t)k * kPListCap + slot] = (uint16_t)k2;
-                    upkeep(k2);
-                }
-                np += __popcll(hm);
-            }
-        }
-        if (lane == 0 && np) {
-            c.pcnt[k] = np;
-            if (np > kPListCap) *c.povf = 1;
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        const int cw = lane + 64 * t;
-        if (cw < Wc) {
-            gp[cw] = 0ull;
-            gp[Wc + cw] = (cw == (a >> 6)) ? (1ull << (a & 63)) : 0ull;
-        }
-    }
-    // this target's x column is never read again
-    if (lane == 0) c.tm[a] = -1;
-    if (lane == 0) {
-        atomicAdd(&c.lcnt[0], 1u);
-        atomicAdd(&c.lcnt[1], (unsigned int)nrows);
-    }
-}
-
-// Load one row's words for this lane (from global or LDS).
-template <int WPL>
-__device__ __forceinline__ void load_row_lane(const uint64_t* row, int Wc, int lane, uint64_t* x, uint64_t* z)
-{
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        const int cw = lane + 64 * t;
-        const bool in = cw < Wc;
-        x[t] = in ? row[cw] : 0ull;
-        z[t] = in ? row[Wc + cw] : 0ull;
-    }
-}
-
-// One wave: the whole random measurement of target k (pivot stabilizer index ip).
-template <int WPL>
-__device__ void wave_random(const ChainCtx& c, int k, int ip, const int* rows, int nrows, int lane)
-{
-    const Geom& g = c.g;
-    k = uni(k);
-    ip = uni(ip);
-    nrows = uni(nrows);
-    // the pivot's sign words (first 128 shots), its rs bit and the target's qubit are read
-    // first, then the pivot row: waiting for the row also covers them
-    const uint64_t rd0 = lane < g.bpc ? c.rd[(size_t)(c.s * g.bpc + lane) * g.NB + g.Wr + (ip >> 6)] : 0ull;
-    const uint64_t rd1 =
-        lane + 64 < g.bpc ? c.rd[(size_t)(c.s * g.bpc + 64 + lane) * g.NB + g.Wr + (ip >> 6)] : 0ull;
-    const uint64_t rsw = c.rs[g.Wr + (ip >> 6)];
-    const int a = c.tq[k];
-    uint64_t xp[WPL], zp[WPL];
-    const uint64_t* prow = c.tb + (size_t)(g.NR + ip) * g.RS;
-    // (lanes past Wc load nothing and hold zeros, so nothing waits for the row before the
-    // rowsum rows' loads are issued)
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        xp[t] = zp[t] = 0ull;
-        if (lane + 64 * t < g.Wc) {
-            xp[t] = prow[lane + 64 * t];
-            zp[t] = prow[g.Wc + lane + 64 * t];
-        }
-    }
-    // the outcome draws depend on the key and the target only: made while the loads are in flight
-    const int gb0 = c.s * g.bpc + lane;
-    const int out0 = lane < g.bpc ? outcome_bit(c, k, gb0) : 0;
-    const int out1 = lane + 64 < g.bpc ? outcome_bit(c, k, gb0 + 64) : 0;
-    uint64_t pend[4] = {rsw, rd0, rd1, (uint64_t)(uint32_t)a};
-    rowsum_rows<WPL>(c, xp, zp, pend, ip & 63, rows, nrows, 0, 1, lane);
-    const int rsp = (int)((pend[0] >> (ip & 63)) & 1ull);
-    random_epilogue<WPL>(c, k, (int)(uint32_t)pend[3], ip, rsp, xp, zp, rows, nrows, lane, nullptr, nullptr, 0, true,
-                         pend[1], pend[2], out0, out1);
-}
-
-// Whole block: one target with many stabilizer rows (dense tableaux).  Called by every thread.
-__device__ void block_solo(const ChainCtx& c, int k, uint64_t* sm, int tid, int nt)
-{
-    const Geom& g = c.g;
-    const int lane = tid & 63, wave = uni(tid >> 6), nwaves = nt >> 6;
-    const int Wc = g.Wc, Wr = g.Wr, NB = g.NB, RS = g.RS, K = c.K;
-    const int nrdw = c.nrdw;
-    uint64_t* rowp = sm;
-    uint64_t* sM = rowp + RS;      // stabilizer words w = 0..Wr-1 (rows NR + 64 w ...)
-    uint64_t* sC = sM + Wr;
-    uint64_t* sRdp = sC + Wr;
-    int* nz = (int*)(sRdp + nrdw);
-    __shared__ int s_piv, s_nnz, s_rsp;
-    const int a = c.tq[k];
-    uint64_t* X = c.X;
-    uint64_t* tb = c.tb;
-
-    if (tid == 0) {
-        s_piv = INT_MAX;
-        s_nnz = 0;
-    }
-    __syncthreads();
-    for (int w = tid; w < Wr; w += nt) {
-        const uint64_t v = X[(size_t)(Wr + w) * K + k];
-        if (v) atomicMin(&s_piv, w * 64 + ctz64(v));
-    }
-    __syncthreads();
-    const int ip = uni(s_piv);
-    if (ip == INT_MAX) {
-        // deterministic now: reduced after the layer on the final tableau
-        if (tid == 0) c.cl[k] = -2;
-        __syncthreads();
-        return;
-    }
-    // gather the pivot row and the stabilizer rows with x at the qubit
-    const int wq = ip >> 6;
-    const uint64_t bq = 1ull << (ip & 63);
-    uint64_t* gp = tb + (size_t)(g.NR + ip) * RS;
-    for (int j = tid; j < RS; j += nt) rowp[j] = gp[j];
-    for (int w = tid; w < Wr; w += nt) {
-        uint64_t v = X[(size_t)(Wr + w) * K + k];
-        if (w == wq) v &= ~bq;
-        sM[w] = v;
-        sC[w] = 0;
-        if (v) nz[atomicAdd(&s_nnz, 1)] = w;
-    }
-    for (int t = tid; t < nrdw; t += nt) sRdp[t] = 0;
-    if (tid == 0) s_rsp = (int)((c.rs[Wr + wq] >> (ip & 63)) & 1ull);
-    __syncthreads();
-    // per-shot pivot signs; rowsum(i, p), one row per wave at a time
-    for (int b = tid; b < g.bpc; b += nt) {
-        const uint64_t bit = (c.rd[(size_t)(c.s * g.bpc + b) * NB + Wr + wq] >> (ip & 63)) & 1ull;
-        if (bit) atomicOr((unsigned long long*)&sRdp[b >> 6], 1ull << (b & 63));
-    }
-    const int nnz = uni(s_nnz);
-    int idx = 0;
-    for (int t = 0; t < nnz; ++t) {
-        const int w = nz[t];
-        uint64_t v = sM[w];
-        while (v) {
-            const int bit = ctz64(v);
-            v &= v - 1;
-            if ((idx++ % nwaves) != wave) continue;
-            uint64_t* row = tb + (size_t)(g.NR + w * 64 + bit) * RS;
-            int G = 0;
-            for (int j = lane; j < Wc; j += 64) {
-                const uint64_t xp = rowp[j], zp = rowp[Wc + j];
-                if ((xp | zp) == 0) continue;
-                const uint64_t xi = row[j], zi = row[Wc + j];
-                G += gsum(xp, zp, xi, zi);
-                row[j] = xi ^ xp;
-                row[Wc + j] = zi ^ zp;
-            }
-            G = wave_sum_uniform(G, lane);
-            if (lane == 0) {
-                if (G & 1) atomicOr(c.err, 4);
-                if (G & 2) atomicOr((unsigned long long*)&sC[w], 1ull << bit);
-            }
-        }
-    }
-    if (tid == 0) {
-        atomicAdd(&c.lcnt[0], 1u);
-        atomicAdd(&c.lcnt[1], (unsigned int)idx);
-    }
-    __syncthreads();
-    // signs of the rowsum rows, pending targets' x columns, the pivot log
-    const int rsp = uni(s_rsp);
-    for (int t = tid; t < nnz; t += nt) {
-        const int w = nz[t];
-        c.rs[Wr + w] ^= (rsp ? sM[w] : 0ull) ^ sC[w];
-    }
-    for (int id = tid; id < nnz * g.bpc; id += nt) {
-        const int b = id / nnz, t = id - b * nnz;
-        if ((sRdp[b >> 6] >> (b & 63)) & 1ull) {
-            const int w = nz[t];
-            c.rd[(size_t)(c.s * g.bpc + b) * NB + Wr + w] ^= sM[w];
-        }
-    }
-    for (int j = tid; j < Wc; j += nt) {
-        uint64_t bits = rowp[j];
-        while (bits) {
-            const int bit = ctz64(bits);
-            bits &= bits - 1;
-            const int k2 = c.tm[j * 64 + bit];
-            if (k2 < 0 || k2 == k) continue;
-            plist_add(c, k, k2);
-            uint64_t* X2 = X + k2;
-            for (int t = 0; t < nnz; ++t) X2[(size_t)(Wr + nz[t]) * K] ^= sM[nz[t]];
-            X2[(size_t)(Wr + wq) * K] &= ~bq;
-        }
-    }
-    uint64_t* lrow = c.lrow + (size_t)k * RS;
-    for (int j = tid; j < RS; j += nt) lrow[j] = rowp[j];
-    for (int t = tid; t < nrdw; t += nt) c.lrd[(size_t)k * nrdw + t] = sRdp[t];
-    if (tid == 0) {
-        c.lrs[k] = rsp;
-        c.lp[k] = ip;
-        *c.ran = 1;
-    }
-    __syncthreads();
-    // p <- Z_a with the outcome as its sign
-    const int za = Wc + (a >> 6);
-    for (int j = tid; j < RS; j += nt) gp[j] = (j == za) ? (1ull << (a & 63)) : 0ull;
-    if (tid == 0) c.rs[Wr + wq] &= ~bq;
-    for (int b = tid; b < g.bpc; b += nt) {
-        const int gb = c.s * g.bpc + b;
-        const int out = outcome_bit(c, k, gb);
-        uint64_t* rdb = c.rd + (size_t)gb * NB;
-        rdb[Wr + wq] = (rdb[Wr + wq] & ~bq) | (out ? bq : 0ull);
-        c.obuf[(size_t)gb * K + k] = (uint8_t)out;
-    }
-    if (tid == 0) c.tm[a] = -1;
-    __syncthreads();
-}
-
-// WPL = column words per lane of a row, ceil(Wc / 64) (= stabilizer bands per lane): the
-// one-wave paths keep that many words of the pivot and of a batch of rows in registers, so
-// narrow tableaux get a kernel without the registers the widest one needs, and room for twelve
-// waves instead of eight (more of a round's targets run at once).
-constexpr int chain_threads(int wpl) { return wpl == 1 ? 768 : 512; }
-template <int WPL>
-__global__ void __launch_bounds__(chain_threads(WPL))
-k_chain(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs, uint64_t* __restrict__ rd,
-        uint64_t* __restrict__ Xcol, uint64_t* __restrict__ Zcol, int K,
-        int* __restrict__ cls, const int* __restrict__ tq, int* __restrict__ pend, uint64_t seed, uint64_t first_shot, uint64_t instr, int pos_base,
-        int* __restrict__ plog_p, uint64_t* __restrict__ plog_row, int* __restrict__ plog_rs,
-        uint64_t* __restrict__ plog_rd, int* __restrict__ ran, uint16_t* __restrict__ plist,
-        int* __restrict__ pcnt, int* __restrict__ povf, uint8_t* __restrict__ obuf,
-        int* __restrict__ err, unsigned long long* __restrict__ counters)
-{
-    extern __shared__ uint64_t sm[];
-    const int s = blk_x(g);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = uni(tid >> 6), nwaves = nt >> 6;
-    const ChainLds L = chain_lds_layout(g);
-    int* owner = (int*)((char*)sm + L.owner);
-    // window entries live in fixed slots; wpos[] lists the slots in op order
-    int* sk = (int*)((char*)sm + L.win);   // target id per slot
-    int* stype = sk + kWin;                 // T_RANDOM, T_BIG_RANDOM, T_UNKNOWN, T_DEAD
-    int* spiv = stype + kWin;
-    int* scnt = spiv + kWin;
-    int* wpos = scnt + kWin;                // window order -> slot
-    int* wsel = wpos + kWin;                // per window position: selected this round
-    int* wstale = wsel + kWin;              // per window position: must be analysed again
-    int* selpos = wstale + kWin;            // positions selected this round
-    int* alist = selpos + kWin;             // slots analysed this round
-    int* srows = alist + kWin;              // kWin * kRCap
-    uint64_t* wideP = (uint64_t*)((char*)sm + L.wide);   // kWide pivot rows
-    uint64_t* wlm = (uint64_t*)((char*)sm + L.words);     // kWide x kRCap word masks
-    int* wlw = (int*)(wlm + kWide * kRCap);               // and their word indices
-    int* aff = (int*)((char*)sm + L.aff);                 // kAffCap x {code, flags, j}
-    __shared__ int s_cnt[16], s_nwin, s_tail, s_bar, s_nsel, s_na, s_aff, s_rsp[kWide], s_wln[kWide];
-    // bit i: row pair i is the pivot of a target executed this round (set and cleared in selection)
-    unsigned int* pbit = (unsigned int*)((char*)sm + L.pbit);
-
-    ChainCtx c;
-    c.g = g;
-    c.tb = tab + (size_t)s * 2 * g.NR * g.RS;
-    c.rs = rs + (size_t)s * g.NB;
-    c.rd = rd;
-    c.X = Xcol + (size_t)s * g.NB * K;
-    c.Z = Zcol + (size_t)s * g.NB * K;
-    c.K = K;
-    c.s = s;
-    c.tq = tq;
-    c.tm = (int16_t*)((char*)sm + L.tm);
-    c.cl = cls + (size_t)s * K;
-    c.nrdw = (g.bpc + 63) >> 6;
-    c.lp = plog_p + (size_t)s * K;
-    c.lrow = plog_row + (size_t)s * K * g.RS;
-    c.lrs = plog_rs + (size_t)s * K;
-    c.lrd = plog_rd + (size_t)s * K * c.nrdw;
-    c.ran = ran;
-    c.plist = plist + (size_t)s * K * kPListCap;
-    c.pcnt = pcnt + (size_t)s * K;
-    c.povf = povf + s;
-    c.seed = seed;
-    c.first_shot = first_shot;
-    c.instr = instr;
-    c.pos_base = pos_base;
-    c.obuf = obuf;
-    c.err = err;
-    c.counters = counters;
-    __shared__ unsigned int s_lcnt[2];
-    c.lcnt = s_lcnt;
-    if (tid == 0) {
-        s_lcnt[0] = 0;
-        s_lcnt[1] = 0;
-    }
-    int* pd = pend + (size_t)s * K;
-    int* cl = cls + (size_t)s * K;
-
-    // a layer with no random target at its start (most of them) ends here, after one pass of
-    // independent loads (nothing runs, so nothing downstream reads the log)
-    {
-        bool any = false;
-        for (int k0 = 0; k0 < K; k0 += 8 * nt) {
-            int v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * nt + tid;
-                v[u] = k < K ? cl[k] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) any |= v[u] >= 0;
-        }
-        if (!__syncthreads_or(any)) return;
-    }
-    // no target of this layer has run yet (the replay reads the log)
-    for (int k = tid; k < K; k += nt) {
-        c.lp[k] = -1;
-        c.pcnt[k] = 0;
-    }
-    if (tid == 0) *c.povf = 0;
-    // pending list: random-at-start targets in op order (stable compaction)
-    int base = 0;
-    for (int k0 = 0; k0 < K; k0 += nt) {
-        const int k = k0 + tid;
-        const bool f = k < K && cl[k] >= 0;
-        const uint64_t m = __ballot(f);
-        const int rank = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) s_cnt[wave] = __popcll(m);
-        __syncthreads();
-        int before = 0, total = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            if (w < wave) before += s_cnt[w];
-            total += s_cnt[w];
-        }
-        if (f) pd[base + before + rank] = k;
-        base += total;
-        __syncthreads();
-    }
-    const int npend = base;
-    if (npend == 0) return;
-    // column upkeep: the x columns of pending random targets
-    for (int q = tid; q < g.n; q += nt) c.tm[q] = -1;
-    __syncthreads();
-    for (int k = tid; k < K; k += nt)
-        if (cl[k] >= 0) c.tm[tq[k]] = (int16_t)k;
-    // owner[i]: (round << 7) | (127 - t) of the first window position t that claimed row pair i
-    // in that round; a claim from an earlier round counts as no claim, so nothing is reset
-    for (int i = tid; i < g.NR; i += nt) owner[i] = 0;
-    for (int i = tid; i < (g.NR + 31) / 32; i += nt) pbit[i] = 0u;
-    const int w0 = min(kWin, npend);
-    for (int t = tid; t < w0; t += nt) {
-        sk[t] = pd[t];
-        stype[t] = T_UNKNOWN;
-        wpos[t] = t;
-    }
-    if (tid == 0) {
-        s_nwin = w0;
-        s_tail = w0;
-    }
-    __syncthreads();
-    int rounds = 0;
-
-    // a round can empty the window; the refill below brings in the next pending targets
-    while (s_nwin > 0 || s_tail < npend) {
-        ++rounds;
-        const int nwin = uni(s_nwin);
-        // ---- analysis: the first kAnalyze entries not yet analysed (new, or touched) ----
-        if (wave == 0) {
-            const bool un = lane < nwin && stype[wpos[lane]] == T_UNKNOWN;
-            const uint64_t m = __ballot(un);
-            const int rank = __popcll(m & ((1ull << lane) - 1ull));
-            if (un && rank < kAnalyze) alist[rank] = wpos[lane];
-            if (lane == 0) s_na = min(__popcll(m), kAnalyze);
-        }
-        __syncthreads();
-        // the stabilizer half of an entry's column (band Wr + lane + 64 u), all words at once;
-        // a wave's next entry is read while it works on the current one (lanes past Wr read
-        // band Wr and are masked)
-        const int na = uni(s_na);
-        auto load_col = [&](int a_i, uint64_t* cw) {
-            const int kk = a_i < na ? sk[alist[a_i]] : 0;
-#pragma unroll
-            for (int u = 0; u < WPL; ++u) {
-                const int w = lane + 64 * u;
-                cw[u] = c.X[(size_t)(g.Wr + (w < g.Wr ? w : 0)) * K + kk];
-            }
-        };
-        uint64_t cwn[WPL];
-        if (wave < na) load_col(wave, cwn);
-        for (int a_i = wave; a_i < na; a_i += nwaves) {
-            const int sl = alist[a_i];
-            const int k = sk[sl];
-            uint64_t cw[WPL];
-#pragma unroll
-            for (int u = 0; u < WPL; ++u) cw[u] = lane + 64 * u < g.Wr ? cwn[u] : 0ull;
-            if (a_i + nwaves < na) load_col(a_i + nwaves, cwn);
-            // pivot = first set bit in band order, the other set bits are the rowsum rows
-            // (ascending); the few nonzero words are read out one by one with scalar loops
-            int pv = INT_MAX, cnt = 0;
-#pragma unroll
-            for (int u = 0; u < WPL; ++u) {
-                uint64_t lanes = __ballot(cw[u] != 0ull);
-                while (lanes) {
-                    const int l = ctz64(lanes);
-                    lanes &= lanes - 1;
-                    uint64_t v = readlane_u64(cw[u], l);
-                    const int wb = l + 64 * u;                 // stabilizer band
-                    if (pv == INT_MAX) {
-                        pv = wb * 64 + ctz64(v);
-                        v &= v - 1;
-                    }
-                    while (v && cnt < kRCap) {
-                        const int bit = ctz64(v);
-                        v &= v - 1;
-                        if (lane == 0) srows[sl * kRCap + cnt] = (g.Wr + wb) * 64 + bit;
-                        ++cnt;
-                    }
-                    cnt += __popcll(v);                        // beyond kRCap: counted only
-                }
-            }
-            if (pv == INT_MAX) {
-                // deterministic now: evaluated after the chain
-                if (lane == 0) {
-                    stype[sl] = T_DEAD;
-                    cl[k] = -2;
-                }
-                continue;
-            }
-            if (lane == 0) {
-                stype[sl] = cnt > kRCap ? T_BIG_RANDOM : T_RANDOM;
-                spiv[sl] = pv;
-                scnt[sl] = cnt;
-            }
-        }
-        __syncthreads();
-        // ---- drop entries that turned deterministic, refill from the pending list ----
-        if (wave == 0) {
-            const int sl = lane < nwin ? wpos[lane] : -1;
-            const bool keep = sl >= 0 && stype[sl] != T_DEAD;
-            const uint64_t m = __ballot(keep);
-            const int nkeep = __popcll(m);
-            const uint64_t usedmask = wave_or(keep ? (1ull << sl) : 0ull);
-            const int tail = uni(s_tail);
-            const int nnew = min(kWin - nkeep, npend - tail);
-            const uint64_t freem = ~usedmask;
-            const bool fr = (freem >> lane) & 1ull;                   // lane = a free slot
-            const int r = __popcll(freem & ((1ull << lane) - 1ull));   // its rank among free slots
-            const int kp = __popcll(m & ((1ull << lane) - 1ull));
-            // every lane has read what it needs; now write the new order
-            __builtin_amdgcn_wave_barrier();
-            if (keep) wpos[kp] = sl;
-            if (fr && r < nnew) {
-                wpos[nkeep + r] = lane;
-                sk[lane] = pd[tail + r];
-                stype[lane] = T_UNKNOWN;
-            }
-            if (lane == 0) {
-                s_nwin = nkeep + nnew;
-                s_tail = tail + nnew;
-            }
-        }
-        __syncthreads();
-        const int nw = uni(s_nwin);
-        if (nw == 0) break;
-        // ---- selection, by wave 0 with one lane per window position t: only analysed
-        // entries before the first unknown or big one are eligible; an eligible entry runs iff
-        // it is the first owner of all its row pairs.  An entry that does not run must be analysed
-        // again iff the pivot of one that runs is among its rows (a row that runs' rowsums touch
-        // changes its x at this entry's qubit only by that pivot's, which is then 0); big
-        // entries (incomplete row lists) whenever anything runs.
-        if (wave == 0) {
-            const int t = lane;
-            const int sl = t < nw ? wpos[t] : 0;
-            const int ty = t < nw ? stype[sl] : T_UNKNOWN;
-            const uint64_t um = __ballot(ty == T_UNKNOWN || ty == T_BIG_RANDOM);
-            const int bar = um ? min(ctz64(um), nw) : nw;
-            const bool elig = t < bar;
-            const int cnt = (t < nw && ty == T_RANDOM) ? scnt[sl] : -1;
-            const int pv = cnt >= 0 ? spiv[sl] : 0;
-            const int* rw = srows + sl * kRCap;
-            const int mine = (rounds << 7) | (127 - t);
-            if (elig)
-                for (int r = 0; r <= cnt; ++r) atomicMax(&owner[r < cnt ? rw[r] - g.NR : pv], mine);
-            __builtin_amdgcn_wave_barrier();
-            bool ok = elig;
-            if (elig)
-                for (int r = 0; r <= cnt && ok; ++r)
-                    if (owner[r < cnt ? rw[r] - g.NR : pv] != mine) ok = false;
-            const uint64_t selm = __ballot(ok);
-            if (t < nw) wsel[t] = ok ? 1 : 0;
-            if (ok) atomicOr(&pbit[pv >> 5], 1u << (pv & 31));
-            __builtin_amdgcn_wave_barrier();
-            bool st = false;
-            if (!ok && cnt >= 0)
-                for (int r = 0; r <= cnt && !st; ++r) {
-                    const int q = r < cnt ? rw[r] - g.NR : pv;
-                    if ((pbit[q >> 5] >> (q & 31)) & 1u) st = true;
-                }
-            __builtin_amdgcn_wave_barrier();
-            if (ok) atomicAnd(&pbit[pv >> 5], ~(1u << (pv & 31)));
-            if (t < nw && (st || (ty == T_BIG_RANDOM && bar > 0))) stype[sl] = T_UNKNOWN;
-            if (ok) selpos[__popcll(selm & ((1ull << lane) - 1ull))] = t;
-            if (lane == 0) {
-                s_bar = bar;
-                s_nsel = __popcll(selm);
-                s_aff = 0;
-            }
-        }
-        __syncthreads();
-        const int bar = uni(s_bar);
-        const int nsel = uni(s_nsel);
-        // ---- execution ----
-        if (bar == 0 && stype[wpos[0]] == T_BIG_RANDOM) {
-            block_solo(c, sk[wpos[0]], sm, tid, nt);
-            if (tid == 0) {
-                wsel[0] = 1;
-                count_add(counters, 1, 1ull);
-            }
-            // a dense update may touch anything: analyse every remaining entry again
-            for (int t = tid + 1; t < nw; t += nt) stype[wpos[t]] = T_UNKNOWN;
-        } else if (nsel <= kWide) {
-            // few targets: stage their pivot rows, spread their rowsums over all waves, and
-            // hand their column upkeep to the whole block
-            for (int id = tid; id < nsel * g.RS; id += nt) {
-                const int j = id / g.RS, w = id - j * g.RS;
-                const int ip = spiv[wpos[selpos[j]]];
-                wideP[j * g.RS + w] = c.tb[(size_t)(g.NR + ip) * g.RS + w];
-            }
-            if (tid < nsel) {
-                const int ip = spiv[wpos[selpos[tid]]];
-                s_rsp[tid] = (int)((c.rs[g.Wr + (ip >> 6)] >> (ip & 63)) & 1ull);
-            }
-            // word lists of the rowsum rows: wave j writes target j's runs
-            for (int j = wave; j < nsel; j += nwaves) {
-                const int sl = wpos[selpos[j]];
-                uint64_t hm[2], mv[2];
-                int wv[2];
-                row_runs(srows + sl * kRCap, scnt[sl], lane, hm, wv, mv);
-                const int n0 = __popcll(hm[0]);
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if ((hm[h] >> lane) & 1ull) {
-                        const int pos = (h ? n0 : 0) + __popcll(hm[h] & ((1ull << lane) - 1ull));
-                        wlw[j * kRCap + pos] = wv[h];
-                        wlm[j * kRCap + pos] = mv[h];
-                    }
-                if (lane == 0) s_wln[j] = n0 + __popcll(hm[1]);
-            }
-            __syncthreads();
-            for (int j = 0; j < nsel; ++j) {
-                const int sl = wpos[selpos[j]];
-                if (wave >= scnt[sl]) continue;
-                uint64_t xp[WPL], zp[WPL];
-                load_row_lane<WPL>(wideP + j * g.RS, g.Wc, lane, xp, zp);
-                uint64_t pend[1] = {(uint64_t)s_rsp[j]};
-                rowsum_rows<WPL>(c, xp, zp, pend, 0, srows + sl * kRCap, scnt[sl], wave, nwaves, lane);
-            }
-            for (int j = wave; j < nsel; j += nwaves) {
-                const int sl = wpos[selpos[j]];
-                uint64_t xp[WPL], zp[WPL];
-                load_row_lane<WPL>(wideP + j * g.RS, g.Wc, lane, xp, zp);
-                random_epilogue<WPL>(c, sk[sl], c.tq[sk[sl]], spiv[sl], s_rsp[j], xp, zp, srows + sl * kRCap, scnt[sl], lane,
-                                aff, &s_aff, j);
-            }
-            __syncthreads();
-            // column upkeep of the batch: (entry, word) pairs over the block; the extra slot
-            // u == maxw clears the pivot's bit
-            const int naff = min(s_aff, kAffCap);
-            int maxw = 0;
-            for (int j = 0; j < nsel; ++j) maxw = max(maxw, s_wln[j]);
-            for (int id = tid; id < naff * (maxw + 1); id += nt) {
-                const int e = id / (maxw + 1), u = id - e * (maxw + 1);
-                const int k2 = aff[3 * e], j = aff[3 * e + 2];
-                unsigned long long* X2 = (unsigned long long*)(c.X + k2);
-                if (u < maxw) {
-                    if (u >= s_wln[j]) continue;
-                    atomicXor(&X2[(size_t)wlw[j * kRCap + u] * K], (unsigned long long)wlm[j * kRCap + u]);
-                } else {
-                    const int ip = spiv[wpos[selpos[j]]];
-                    atomicAnd(&X2[(size_t)(g.Wr + (ip >> 6)) * K], ~(1ull << (ip & 63)));
-                    plist_add(c, sk[wpos[selpos[j]]], k2);
-                }
-            }
-        } else {
-            for (int j = wave; j < nsel; j += nwaves) {
-                const int sl = wpos[selpos[j]];
-                wave_random<WPL>(c, sk[sl], spiv[sl], srows + sl * kRCap, scnt[sl], lane);
-            }
-        }
-        __syncthreads();
-        // ---- remove executed entries (their slots become free) ----
-        if (wave == 0) {
-            const bool keep = lane < nw && !wsel[lane];
-            const int sl = lane < nw ? wpos[lane] : 0;
-            const uint64_t m = __ballot(keep);
-            const int rank = __popcll(m & ((1ull << lane) - 1ull));
-            __builtin_amdgcn_wave_barrier();
-            if (keep) wpos[rank] = sl;
-            if (lane == 0) s_nwin = __popcll(m);
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        count_add(counters, 0, (unsigned long long)rounds);
-        count_add(counters, 4, (unsigned long long)s_lcnt[0]);
-        count_add(counters, 5, (unsigned long long)s_lcnt[1]);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// Destabilizer replay of a measurement layer: grid (Wr destabilizer bands, S copies), 512
-// threads.  In op order, every target the chain ran did, to each destabilizer D with x at its
-// qubit, rowsum(D, P) with its old pivot row P (sign r_D <- r_D ^ r_P ^ (i-power / 2), the
-// per-shot parts XOR), and replaced its pivot's own destabilizer by P.  Only rows with x at
-// some run target at layer start, or a pivot's partner, can be touched.
-//
-// Which targets hit D depends only on D's x bits at the run targets' qubits; applying P flips
-// exactly the bits of the pending targets the chain listed for P (a target run earlier has no
-// x in P: P commutes with its Z), and replacing D by P sets them to P's.  So the hits of all
-// 64 rows of the band are found at once, bit-sliced: word V[j] holds the band's x bits at run
-// target j, and one wave walks the run targets in order with the next 64 words in a ring of
-// lanes (flips to words within the ring land in registers, flips beyond it are LDS atomics),
-// leaving H[j] = the rows target j hits (in place of V[j]).  Runs of targets that hit nothing
-// are skipped a ring at a time.  Then every wave takes rows: a row's events (its replacement,
-// if it is a partner, and the hits after it) are read off H with ballots and applied to its
-// x and z words with kReplayAhead pivot rows in flight, summing the i-powers per lane (every
-// step's power is even, so the halves add); the signs of the events after the replacement
-// XOR in any order and are taken in parallel over the lanes.  When a pivot's list overflowed
-// or the lists do not fit in LDS, a wave instead tests its row's live bits 64 run targets at a
-// time and applies each hit before testing again.
-// ------------------------------------------------------------------------------------------
-constexpr int kReplayEvents = 512;     // events a wave collects before applying them
-// pivot rows in flight per wave while events are applied (a ring of register buffers)
-template <int WPL> struct ReplayRing { static constexpr int depth = WPL <= 2 ? 16 : WPL == 3 ? 12 : 8; };
-constexpr int kReplayInline = 3;       // list entries kept in a target's descriptor
-
-// Dynamic LDS of the replay.  With lists (ent_cap >= 0): per-shot deltas, partner table, run
-// targets, then per run target its x word V (H after the walk) and its descriptor, the
-// target -> run index map, the per-wave event lists, then ent_cap entries of the long lists.
-// Without: the first three only.
-struct ReplayLds {
-    int acc, prow, rk, V, desc, jmap, ev, ent;      // byte offsets
-    int small_bytes;                                // end of the form without lists
-    int fixed_bytes;                                // end of the form with lists, before entries
-};
-
-__host__ __device__ inline ReplayLds replay_lds_layout(int K, int nrdw, int nwaves)
-{
-    ReplayLds L;
-    int o = 0;
-    L.acc = o; o += nwaves * nrdw * 8;
-    L.prow = o; o += 64 * 4;
-    L.rk = o; o += ((K * 4 + 7) / 8) * 8;
-    L.small_bytes = o;
-    L.V = o; o += K * 8;
-    L.desc = o; o += K * 8;
-    L.jmap = o; o += ((K * 2 + 7) / 8) * 8;
-    L.ev = o; o += nwaves * kReplayEvents * 4;
-    L.ent = o;
-    L.fixed_bytes = o;
-    return L;
-}
-
-// Whether the run-index map (16-bit) covers every target.
-__host__ __device__ inline bool replay_walk_fits(int K) { return K <= 32767; }
-
-// Row words of this lane (word lane + 64 t, WPL slots).  No load is conditional, so that the
-// loads of rows in flight are waited for one by one: the last slot's lanes past Wc load word 0
-// instead (any address of the row does) and the caller masks them with the tail mask.
-template <int WPL>
-__device__ __forceinline__ void replay_load(const uint64_t* row, int Wc, int lane, uint64_t* x, uint64_t* z)
-{
-#pragma unroll
-    for (int t = 0; t < WPL; ++t) {
-        const int cw = (t < WPL - 1 || lane + 64 * t < Wc) ? lane + 64 * t : 0;
-        x[t] = row[cw];
-        z[t] = row[Wc + cw];
-    }
-}
-
-// Descriptor of run target j: bits 0..47 up to kReplayInline later run indices of its list
-// (16 bits each) or, for a longer list, its offset in the entry area (bits 0..31); bits 48..52
-// the list length; bits 53..59 its partner row in the band + 1 (0: the partner is elsewhere).
-__device__ __forceinline__ int desc_len(uint64_t d) { return (int)((d >> 48) & 31); }
-__device__ __forceinline__ int desc_partner(uint64_t d) { return (int)((d >> 53) & 127) - 1; }
-
-template <int WPL>
-__global__ void __launch_bounds__(512)
-k_replay(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs, uint64_t* __restrict__ rd,
-         const uint64_t* __restrict__ Xcol, int K, const int* __restrict__ tq,
-         const int* __restrict__ plog_p, const uint64_t* __restrict__ plog_row,
-         const int* __restrict__ plog_rs, const uint64_t* __restrict__ plog_rd,
-         const uint16_t* __restrict__ plist, const int* __restrict__ pcnt, const int* __restrict__ povf,
-         const int* __restrict__ ran, int ent_cap, int* __restrict__ err, unsigned long long* __restrict__ counters)
-{
-    if (*ran == 0) return;                             // no random target ran in this layer
-    extern __shared__ uint64_t rsm[];
-    const int band = blk_x(g), s = blk_y(g);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6, nwaves = nt >> 6;
-    const int Wc = g.Wc, RS = g.RS, NB = g.NB;
-    const int nrdw = (g.bpc + 63) >> 6;
-    const uint64_t tail = lane + 64 * (WPL - 1) < Wc ? ~0ull : 0ull;   // last slot in the row
-    const ReplayLds LL = replay_lds_layout(K, nrdw, nwaves);
-    char* base = (char*)rsm;
-    const bool lists = ent_cap >= 0;                     // LDS holds the list form
-    uint64_t* acc = (uint64_t*)(base + LL.acc);          // nwaves x nrdw per-shot sign deltas
-    int* prow = (int*)(base + LL.prow);                  // per row of the band: see below
-    int* rk = (int*)(base + LL.rk);
-    uint64_t* V = lists ? (uint64_t*)(base + LL.V) : nullptr;
-    uint64_t* desc = lists ? (uint64_t*)(base + LL.desc) : nullptr;
-    int16_t* jmap = lists ? (int16_t*)(base + LL.jmap) : nullptr;
-    int* evs = lists ? (int*)(base + LL.ev) : nullptr;
-    uint16_t* ent = lists ? (uint16_t*)(base + LL.ent) : nullptr;
-    __shared__ int s_cnt[16], s_crow[64], s_ncand, s_next;
-    __shared__ unsigned long long s_cand;
-    __shared__ unsigned int s_rc[4];   // work counters, flushed once per block
-    const int* lp = plog_p + (size_t)s * K;
-    const uint16_t* pl = plist + (size_t)s * K * kPListCap;
-    const int* pc = pcnt + (size_t)s * K;
-    const uint64_t* X = Xcol + (size_t)s * NB * K + (size_t)band * K;
-    uint64_t* tb = tab + (size_t)s * 2 * g.NR * RS;
-    uint64_t* rsc = rs + (size_t)s * NB;
-
-    // run targets in op order (stable compaction)
-    if (tid == 0) {
-        s_cand = 0;
-        s_next = 0;
-        s_rc[0] = s_rc[1] = s_rc[2] = s_rc[3] = 0;
-    }
-    for (int r = tid; r < 64; r += nt) prow[r] = -1;
-    __syncthreads();
-    int R = 0;
-    for (int k0 = 0; k0 < K; k0 += nt) {
-        const int k = k0 + tid;
-        const bool f = k < K && lp[k] >= 0;
-        const uint64_t m = __ballot(f);
-        const int rank = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) s_cnt[wave] = __popcll(m);
-        __syncthreads();
-        int before = 0, total = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            if (w < wave) before += s_cnt[w];
-            total += s_cnt[w];
-        }
-        if (f) rk[R + before + rank] = k;
-        R += total;
-        __syncthreads();
-    }
-    if (R == 0) return;
-    // the list form holds for this copy when no pending list overflowed and the long lists fit
-    bool walk = lists && povf[s] == 0;
-    uint64_t cand = 0;
-    if (walk) {
-        for (int k = tid; k < K; k += nt) jmap[k] = -1;
-        __syncthreads();
-        for (int j = tid; j < R; j += nt) jmap[rk[j]] = (int16_t)j;
-        __syncthreads();
-        // descriptors (list entries as run indices; entries that did not run are dropped),
-        // x words, partners; long lists go to ent at offsets from an exclusive scan
-        int T = 0;
-        for (int j0 = 0; j0 < R; j0 += nt) {
-            const int j = j0 + tid;
-            int len = 0, n2 = 0, pr = -1;
-            const uint16_t* lst = nullptr;
-            if (j < R) {
-                const int k = rk[j];
-                lst = pl + (size_t)k * kPListCap;
-                n2 = min(pc[k], kPListCap);
-                for (int e = 0; e < n2; ++e) len += jmap[lst[e]] >= 0 ? 1 : 0;
-                const uint64_t xw = X[k];
-                V[j] = xw;
-                cand |= xw;
-                const int p = lp[k];
-                if ((p >> 6) == band) {
-                    pr = p & 63;
-                    prow[pr] = j;
-                    cand |= 1ull << pr;
-                }
-            }
-            const int big = len > kReplayInline ? len : 0;
-            const int ex = wave_excl_scan(big, lane);
-            if (lane == 0) s_cnt[wave] = wave_sum(big);
-            __syncthreads();
-            int before = 0, total = 0;
-            for (int w = 0; w < nwaves; ++w) {
-                if (w < wave) before += s_cnt[w];
-                total += s_cnt[w];
-            }
-            if (j < R) {
-                uint64_t d = ((uint64_t)len << 48) | ((uint64_t)(pr + 1) << 53);
-                const int o = T + before + ex;
-                if (big) d |= (uint32_t)o;
-                for (int e = 0, n = 0; e < n2; ++e) {
-                    const int jj = jmap[lst[e]];
-                    if (jj < 0) continue;
-                    if (!big) d |= (uint64_t)jj << (16 * n);
-                    else if (o + n < ent_cap) ent[o + n] = (uint16_t)jj;
-                    ++n;
-                }
-                desc[j] = d;
-            }
-            T += total;
-            __syncthreads();
-        }
-        walk = T <= ent_cap;
-    } else {
-        for (int j = tid; j < R; j += nt) {
-            const int k = rk[j];
-            cand |= X[k];
-            const int p = lp[k];
-            if ((p >> 6) == band) {
-                cand |= 1ull << (p & 63);
-                prow[p & 63] = k;
-            }
-        }
-    }
-    cand = wave_or(cand);
-    if (lane == 0 && cand) atomicOr(&s_cand, (unsigned long long)cand);
-    __syncthreads();
-
-    if (walk) {
-        // bit-sliced walk, 64 run targets at a time: lane l holds target j0 + l (its word and
-        // descriptor); flips to targets of the same 64 land in registers, later ones are LDS
-        // atomics made before those targets are read.  A row's bits only ever change by its
-        // own hits and replacement, so each wave walks its own slice of the 64 rows (bits gm of
-        // every word) on its own: its updates touch no other wave's bits.
-        const int rpw = 64 / nwaves;
-        const uint64_t gm = (rpw == 64 ? ~0ull : ((1ull << rpw) - 1ull)) << (rpw * wave);
-        for (int j0 = 0; j0 < R; j0 += 64) {
-            const int jl = j0 + lane;
-            const uint64_t raw = jl < R ? V[jl] & gm : 0ull;
-            uint64_t val = raw;
-            const uint64_t dsc = jl < R ? desc[jl] : 0ull;
-            const int pl_ = desc_partner(dsc);
-            const uint64_t pm = __ballot(jl < R && pl_ >= 0 && ((gm >> pl_) & 1ull));
-            int off = 0;
-            while (true) {
-                // next target from off on that hits a row or has its partner here
-                const uint64_t am = (__ballot(val != 0ull) | pm) & (off < 64 ? ~0ull << off : 0ull);
-                if (!am) break;
-                const int cj = ctz64(am);
-                const uint64_t cur = readlane_u64(val, cj);
-                const uint64_t d = readlane_u64(dsc, cj);
-                const int len = desc_len(d), prd = desc_partner(d);
-                const int pr = (prd >= 0 && ((gm >> prd) & 1ull)) ? prd : -1;
-                const uint64_t bpr = pr >= 0 ? 1ull << pr : 0ull;
-                const uint64_t hit = cur & ~bpr;
-                if (lane == cj) val = hit;                  // H[j]
-                if (pr >= 0) {
-                    // the partner's bits at later targets become P's: cleared here, set below
-                    if (lane > cj) val &= ~bpr;
-                    for (int w = j0 + 64 + lane; w < R; w += 64) atomicAnd((unsigned long long*)&V[w], ~bpr);
-                }
-                for (int e = 0; e < len; ++e) {
-                    const int j2 = len <= kReplayInline ? (int)((d >> (16 * e)) & 0xffff) : (int)ent[(uint32_t)d + e];
-                    if (j2 < j0 + 64) {
-                        if (lane == j2 - j0) val = (val ^ hit) | bpr;
-                    } else if (lane == 0) {
-                        if (hit) atomicXor((unsigned long long*)&V[j2], hit);
-                        if (bpr) atomicOr((unsigned long long*)&V[j2], bpr);
-                    }
-                }
-                off = cj + 1;
-            }
-            // H of the 64 in this wave's bits (0 where nothing hit)
-            if (jl < R && (raw ^ val)) atomicXor((unsigned long long*)&V[jl], raw ^ val);
-        }
-    }
-    if (tid == 0) {
-        uint64_t c = s_cand;
-        int nc = 0;
-        while (c) {
-            s_crow[nc++] = ctz64(c);
-            c &= c - 1;
-        }
-        s_ncand = nc;
-    }
-    __syncthreads();
-    const int ncand = s_ncand;
-
-    uint64_t* myacc = acc + (size_t)wave * nrdw;
-    int* ev = lists ? evs + (size_t)wave * kReplayEvents : nullptr;
-    int nrows = 0, applied = 0, trows = 0, tev = 0;
-    while (true) {
-        int jr = 0;
-        if (lane == 0) jr = atomicAdd(&s_next, 1);
-        jr = __shfl(jr, 0, 64);
-        if (jr >= ncand) break;
-        ++nrows;
-        const int r = s_crow[jr];
-        const int i = band * 64 + r;                   // destabilizer index
-        uint64_t* row = tb + (size_t)i * RS;
-        uint64_t x[WPL], z[WPL];
-        replay_load<WPL>(row, Wc, lane, x, z);
-        x[WPL - 1] &= tail;
-        z[WPL - 1] &= tail;
-        int sh = (int)((rsc[band] >> r) & 1ull);
-        const int sh0 = sh;
-        for (int u = lane; u < nrdw; u += 64) myacc[u] = 0;
-        bool mod = false;
-        // Phase of the rowsums since the last replacement, telescoped: with |u| the number of
-        // qubits where a row has both x and z, rowsum(D, P) raises i to |P| + |D| + 2 z_P.x_D
-        // - |P D| (mod 4), so the steps from D0 to Dn sum to sum|P| + |D0| - |Dn| + 2 sum z_P.x_D,
-        // and only the parity of the last sum matters: its terms XOR into cr.  G holds
-        // sum|P| + |D0| per lane.
-        int G = 0;
-        uint64_t cr[WPL];
-#pragma unroll
-        for (int t = 0; t < WPL; ++t) {
-            G += __popcll(x[t] & z[t]);
-            cr[t] = 0;
-        }
-        auto phase = [&]() {
-            int v = G;
-#pragma unroll
-            for (int t = 0; t < WPL; ++t) v += 2 * __popcll(cr[t]) - __popcll(x[t] & z[t]);
-            return wave_sum(v);
-        };
-        // D := P_k, signs included (the per-shot deltas make rd's bits equal P's)
-        auto replace_signs = [&](int kk) {
-            const uint64_t* Pd = plog_rd + ((size_t)s * K + kk) * nrdw;
-            sh = plog_rs[(size_t)s * K + kk];
-            for (int b0 = 0; b0 < g.bpc; b0 += 64) {
-                const int b = b0 + lane;
-                const bool cb = b < g.bpc && ((rd[(size_t)(s * g.bpc + b) * NB + band] >> r) & 1ull);
-                const uint64_t m = __ballot(cb);
-                if (lane == 0) myacc[b0 >> 6] = m ^ Pd[b0 >> 6];
-            }
-        };
-        // x and z words of one event: replace (G so far applies to the row being replaced) or
-        // multiply in (the pivot row's last slot is masked here, at use)
-        auto step = [&](bool repl, const uint64_t* px, const uint64_t* pz) {
-            if (repl) {
-                const int Gs = phase();
-                if (lane == 0 && (Gs & 1)) atomicOr(err, 8);
-                G = 0;
-#pragma unroll
-                for (int t = 0; t < WPL; ++t) {
-                    const uint64_t m = t == WPL - 1 ? tail : ~0ull;
-                    x[t] = px[t] & m;
-                    z[t] = pz[t] & m;
-                    G += __popcll(x[t] & z[t]);
-                    cr[t] = 0;
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < WPL; ++t) {
-                    const uint64_t m = t == WPL - 1 ? tail : ~0ull;
-                    const uint64_t a = px[t] & m, b = pz[t] & m;
-                    cr[t] ^= b & x[t];
-                    G += __popcll(a & b);
-                    x[t] ^= a;
-                    z[t] ^= b;
-                }
-                ++applied;
-            }
-        };
-        if (walk) {
-            // events: the replacement (if this row is a partner), then the hits after it
-            const int jp = prow[r];
-            int jn = jp >= 0 ? jp : 0;                 // next run index to read off H
-            bool first = jp >= 0;
-            const uint64_t* prow0 = plog_row + (size_t)s * K * RS;
-            while (true) {
-                int nev = 0;
-                if (first) {
-                    if (lane == 0) ev[0] = rk[jp] | (1 << 30);
-                    nev = 1;
-                    jn = jp + 1;
-                    first = false;
-                }
-                while (jn < R && nev + 64 <= kReplayEvents) {
-                    const int jj = jn + lane;
-                    const bool h = jj < R && ((V[jj] >> r) & 1ull);
-                    const uint64_t hm = __ballot(h);
-                    if (h) ev[nev + __popcll(hm & ((1ull << lane) - 1ull))] = rk[jj];
-                    nev += __popcll(hm);
-                    jn += 64;
-                }
-                if (nev == 0) break;
-                mod = true;
-                // apply in order, the next kReplayAhead pivot rows in flight (a ring of register
-                // buffers rotated by the unrolled loop; loads past the end repeat the last row)
-                constexpr int kReplayAhead = ReplayRing<WPL>::depth;
-                uint64_t px[kReplayAhead][WPL], pz[kReplayAhead][WPL];
-#pragma unroll
-                for (int u = 0; u < kReplayAhead; ++u)
-                    replay_load<WPL>(prow0 + (size_t)(ev[min(u, nev - 1)] & 0x3fffffff) * RS, Wc, lane, px[u], pz[u]);
-                int lastrep = -1;
-                for (int e0 = 0; e0 < nev; e0 += kReplayAhead) {
-#pragma unroll
-                    for (int u = 0; u < kReplayAhead; ++u) {
-                        const int e = e0 + u;
-                        if (e < nev) {
-                            const bool rp = (ev[e] >> 30) & 1;
-                            if (rp) lastrep = e;
-                            step(rp, px[u], pz[u]);
-                        }
-                        const int en = min(e + kReplayAhead, nev - 1);
-                        replay_load<WPL>(prow0 + (size_t)(ev[en] & 0x3fffffff) * RS, Wc, lane, px[u], pz[u]);
-                    }
-                }
-                // signs: from the last replacement on (XOR over events, in any order)
-                if (lastrep >= 0) replace_signs(ev[lastrep] & 0x3fffffff);
-                int par = 0;
-                for (int e = lastrep + 1 + lane; e < nev; e += 64)
-                    par ^= plog_rs[(size_t)s * K + (ev[e] & 0x3fffffff)];
-                sh ^= __popcll(__ballot(par & 1)) & 1;
-                for (int u = 0; u < nrdw; ++u) {
-                    uint64_t a = 0;
-                    for (int e = lastrep + 1 + lane; e < nev; e += 64)
-                        a ^= plog_rd[((size_t)s * K + (ev[e] & 0x3fffffff)) * nrdw + u];
-                    a = wave_xor(a);
-                    if (lane == 0) myacc[u] ^= a;
-                }
-                if (jn >= R) break;
-            }
-        } else {
-            // walk by testing D's live x bits 64 run targets at a time
-            ++trows;
-            for (int j0 = 0; j0 < R; j0 += 64) {
-                const int jj = j0 + lane;
-                int k = 0, a = 0, p = -1;
-                if (jj < R) {
-                    k = rk[jj];
-                    a = tq[k];
-                    p = lp[k];
-                }
-                int from = 0;
-                while (true) {
-                    const int wa = a >> 6, src = wa & 63, slot = wa >> 6;
-                    uint64_t vv = 0;
-#pragma unroll
-                    for (int t = 0; t < WPL; ++t) {
-                        const uint64_t o = shfl_u64(x[t], src);
-                        if (slot == t) vv = o;
-                    }
-                    const bool hit = jj < R && lane >= from && ((((vv >> (a & 63)) & 1ull) != 0) || p == i);
-                    const uint64_t hm = __ballot(hit);
-                    if (!hm) break;
-                    const int l = ctz64(hm);
-                    const int kk = __shfl(k, l, 64), pkk = __shfl(p, l, 64);
-                    uint64_t px[WPL], pz[WPL];
-                    replay_load<WPL>(plog_row + ((size_t)s * K + kk) * RS, Wc, lane, px, pz);
-                    const bool repl = pkk == i;
-                    step(repl, px, pz);
-                    if (repl) {
-                        replace_signs(kk);
-                    } else {
-                        sh ^= plog_rs[(size_t)s * K + kk];
-                        const uint64_t* Pd = plog_rd + ((size_t)s * K + kk) * nrdw;
-                        for (int u = lane; u < nrdw; u += 64) myacc[u] ^= Pd[u];
-                    }
-                    mod = true;
-                    ++tev;
-                    from = l + 1;
-                }
-            }
-        }
-        if (mod) {
-            const int Gs = phase();
-            if (lane == 0 && (Gs & 1)) atomicOr(err, 8);
-            sh ^= (Gs >> 1) & 1;
-#pragma unroll
-            for (int t = 0; t < WPL; ++t) {
-                const int cw = lane + 64 * t;
-                if (cw < Wc) {
-                    row[cw] = x[t];
-                    row[Wc + cw] = z[t];
-                }
-            }
-            if (lane == 0 && sh != sh0) atomicXor((unsigned long long*)&rsc[band], 1ull << r);
-            for (int b = lane; b < g.bpc; b += 64)
-                if ((myacc[b >> 6] >> (b & 63)) & 1ull)
-                    atomicXor((unsigned long long*)&rd[(size_t)(s * g.bpc + b) * NB + band], 1ull << r);
-        }
-    }
-    if (lane == 0 && nrows) {
-        atomicAdd(&s_rc[0], (unsigned int)applied);
-        atomicAdd(&s_rc[1], (unsigned int)nrows);
-        atomicAdd(&s_rc[2], (unsigned int)trows);
-        atomicAdd(&s_rc[3], (unsigned int)tev);
-    }
-    __syncthreads();
-    if (tid == 0 && s_rc[1]) {
-        if (s_rc[0]) count_add(counters, 8, (unsigned long long)s_rc[0]);
-        count_add(counters, 9, (unsigned long long)s_rc[1]);
-        if (s_rc[2]) count_add(counters, 10, (unsigned long long)s_rc[2]);
-        if (s_rc[3]) count_add(counters, 11, (unsigned long long)s_rc[3]);
     }
 }
 
