@@ -95,7 +95,7 @@ int stab_tableau_bytes(int32_t n, int32_t shots, int32_t mode, uint64_t *bytes_o
 int stab_create(int32_t n, int32_t shots, int32_t mode, uint64_t seed, uint64_t first_shot,
                 void *dev_buf, uint64_t buf_bytes, void *hip_stream, stab_ctx **out);
 
-/* Release the context's own scratch memory (the column, pivot-log and record buffers the
+/* Release the context's own scratch memory (the column, window and record buffers the
  * measurement steps of Sec. 2.4 use).  Never frees dev_buf.  NULL is ignored. */
 void stab_destroy(stab_ctx *ctx);
 
@@ -293,9 +293,10 @@ int stab_batch_execute(stab_batch *batch, const stab_batch_program *prog, uint8_
  * takes a whole 64-lane wave, else a row takes the smallest power of two of lanes that holds
  * its x words, so one wave updates several rows of a small circuit per load.  With two x
  * words per lane (a circuit above 4096 qubits in the batch) 8 rows in flight run as 4.  Bit 9
- * (STAB_TILE_ONE_BLOCK): the kernel variant whose registers are sized for one block per compute
- * unit (no spills), else capped so two blocks share one.  0 = the default (8 rows in flight with
- * one x word per lane, 2 with two; lanes sized to the row; two blocks per compute unit).
+ * (STAB_TILE_ONE_BLOCK): the kernel variant with one block of 16 waves per compute unit, else two
+ * blocks of 8 waves share one.  0 = the default (8 rows in flight with one x word per lane, 2 with
+ * two; lanes sized to the row; one block per compute unit for a batch of no more circuits than the
+ * device has compute units, else two).
  * The configuration changes speed only: every configuration writes the same records and
  * leaves the same tableaux. */
 #define STAB_TILE_WHOLE_WAVE 0x100
@@ -332,7 +333,8 @@ int stab_batch_get_tableau(stab_batch *batch, int32_t circuit, uint8_t *x, uint8
 /* Work counters of the batch since creation: [2] deterministic measurements, [4] random
  * measurements, [5] rows updated by rowsum or multiplied by deterministic reductions,
  * [6] bytes the measurements must move (target columns at one 8-byte word per row, pivot
- * row, rowsum rows read and written, row moves; multiplied rows read), [7] bytes of the
+ * rows, the rows a window of random targets changes read and written once, row moves; multiplied
+ * rows read), [7] bytes of the
  * band passes (every row read, and written when a gate changed x|z); the others stay 0.
  * ncounters <= 12. */
 int stab_batch_get_counters(stab_batch *batch, uint64_t *counters, int32_t ncounters);

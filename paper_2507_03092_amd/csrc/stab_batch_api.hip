@@ -28,6 +28,7 @@ struct stab_batch_program {
     std::vector<long long> ninstr;    // instructions per circuit
     std::vector<long long> rec_byte;  // first output byte per circuit (ncirc + 1 entries)
     int lds_bytes = 0;
+    int maxwc = 1;                    // x words of a row of the largest circuit
     int nw = 1;                       // x words per lane (kernel variant)
     int tile = 0;                     // launch configuration (BatchArgs::tile)
     uint64_t shape = 0;               // fingerprint of the program's shape (autotuner cache key)
@@ -79,6 +80,35 @@ int batch_layout(int32_t ncirc, const int32_t* n, BatchLayout& L)
             return fail(STAB_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_));     \
         }                                                                                      \
     } while (0)
+
+// Waves a block of a launch over nc circuits: 16 where a compute unit gets at most one circuit
+// anyway (100 shots of a 1249-qubit circuit with T1/T2 noise: 48 ms against 55 ms), 8 where two
+// share it and fill each other's waits (1024 circuits of 64 to 2048 qubits: 20 against 22 ms).
+int batch_waves(int nc, int tile)
+{
+    if (tile) return (tile & kTileOneBlock) ? 16 : 8;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 8;
+    return nc <= cus ? 16 : 8;
+}
+
+// The batch kernel over nc circuits of at most 64 maxwc qubits.
+void batch_start(BatchArgs A, int nc, int maxwc, int tile, hipStream_t st)
+{
+    const int bw = batch_waves(nc, tile);
+    // what the largest circuit needs, and room for several bands of a pass where that costs no block
+    const size_t lds = std::max((size_t)batch_lds_words(maxwc, bw) * 8, (size_t)(bw == 16 ? kLdsBytes : kLdsBytes / 2));
+    A.lds_words = (int)(lds / 8);
+    if (maxwc <= 64) {
+        if (bw == 16) k_batch<1, 16><<<nc, 1024, lds, st>>>(A);
+        else k_batch<1, 8><<<nc, 512, lds, st>>>(A);
+    } else {
+        if (bw == 16) k_batch<2, 16><<<nc, 1024, lds, st>>>(A);
+        else k_batch<2, 8><<<nc, 512, lds, st>>>(A);
+    }
+}
 
 int batch_init(stab_batch* b)
 {
@@ -177,12 +207,13 @@ int batch_compile_one(int c, int n, const stab_instr* ins, int64_t ninstr, const
             m.rec = recorded ? (int)nrec : -1;
             if (recorded) nrec += nt;
             // distinct qubits: its columns can come out of the band pass before it
-            m.fast = kind != STAB_T1T2 ? 1 : 0;
+            m.fast = 1;
             for (uint32_t q = 0; q < nt && m.fast; ++q) {
                 if (mstamp[t[q]] == (int)k) m.fast = 0;
                 mstamp[t[q]] = (int)k;
             }
-            if (m.fast) kfast = std::max(kfast, (int)nt);
+            // (a T1T2 instruction's events, usually a few, share the scratch of the others)
+            if (m.fast && kind != STAB_T1T2) kfast = std::max(kfast, (int)nt);
             meas_tg.insert(meas_tg.end(), t, t + nt);
             steps.push_back(make_int4(2, (int)meas.size(), 0, 0));
             meas.push_back(m);
@@ -230,7 +261,7 @@ int stab_batch_create(int32_t ncirc, const int32_t* n, uint64_t seed, void* dev_
         hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return fail(STAB_EDEVICE, "no HIP device");
     for (int c = 0; c < ncirc; ++c)
-        if (batch_lds_words((n[c] + 63) / 64) * 8 > lds)
+        if (batch_lds_words((n[c] + 63) / 64, kBatchWavesMax) * 8 > lds)
             return fail(STAB_ERANGE, "circuit " + std::to_string(c) + ": a 64-row band does not fit in LDS");
     stab_batch* b = new stab_batch();
     b->ncirc = ncirc;
@@ -252,10 +283,10 @@ int stab_batch_create(int32_t ncirc, const int32_t* n, uint64_t seed, void* dev_
         C.tab_off = L.tab_off[c];
         C.rs_off = L.rs_off[c];
     }
-    (void)hipFuncSetAttribute((const void*)k_batch<1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_batch<2, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_batch<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_batch<2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<1, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<2, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<1, 16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<2, 16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipGetLastError();
     const bool ok = hipMalloc((void**)&b->d_circ, sizeof(BatchCirc) * ncirc) == hipSuccess &&
                     hipMalloc((void**)&b->d_err, sizeof(int)) == hipSuccess &&
@@ -365,7 +396,8 @@ int stab_batch_compile(stab_batch* b, const stab_instr* instrs, const int64_t* i
     for (int c = 0; c < C; ++c) order[c] = c;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
     if (reverse_blocks()) std::reverse(order.begin(), order.end());
-    P->lds_bytes = batch_lds_words(maxwc) * 8;
+    P->lds_bytes = batch_lds_words(maxwc, kBatchWavesMax) * 8;   // (the wider form's; the check at launch)
+    P->maxwc = maxwc;
     P->nw = maxwc <= 64 ? 1 : 2;
     // shape fingerprint: sizes and per-circuit step, gate and measured-target counts
     {
@@ -472,14 +504,7 @@ int batch_launch(stab_batch* b, const stab_batch_program* P, int tile, int quota
     A.seed = b->seed;
     A.err = b->d_err;
     A.counters = b->d_counters;
-    const bool one = (tile & kTileOneBlock) != 0;
-    if (P->nw == 1) {
-        if (one) k_batch<1, 2><<<b->ncirc, kBatchThreads, P->lds_bytes, b->stream>>>(A);
-        else k_batch<1, 4><<<b->ncirc, kBatchThreads, P->lds_bytes, b->stream>>>(A);
-    } else {
-        if (one) k_batch<2, 2><<<b->ncirc, kBatchThreads, P->lds_bytes, b->stream>>>(A);
-        else k_batch<2, 4><<<b->ncirc, kBatchThreads, P->lds_bytes, b->stream>>>(A);
-    }
+    batch_start(A, b->ncirc, P->maxwc, tile, b->stream);
     BHIP_CHECK(b, hipGetLastError());
     BHIP_CHECK(b, hipEventRecord(b->ev1, b->stream));
     return STAB_OK;

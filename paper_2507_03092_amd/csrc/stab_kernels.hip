@@ -95,27 +95,6 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t v)
     return v;
 }
 
-// In-register transpose of a 64x64 bit matrix held one row per lane (bit c of lane r's word =
-// element (r, c)).  Six butterfly stages swap the off-diagonal blocks of size 32, 16, ..., 1.
-// Every lane of the wave must take part.
-__device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane)
-{
-    const uint64_t masks[6] = {0x00000000FFFFFFFFull, 0x0000FFFF0000FFFFull, 0x00FF00FF00FF00FFull,
-                               0x0F0F0F0F0F0F0F0Full, 0x3333333333333333ull, 0x5555555555555555ull};
-#pragma unroll
-    for (int st = 0; st < 6; ++st) {
-        const int j = 32 >> st;
-        const uint64_t m = masks[st];
-        const uint64_t o = shfl_xor_u64(v, j);
-        if (lane & j) {
-            v ^= ((o >> j) ^ v) & m;
-        } else {
-            v ^= (((v >> j) ^ o) & m) << j;
-        }
-    }
-    return v;
-}
-
 // Sum over the 64 bit positions of g(x1,z1,x2,z2) from the rowsum algorithm (Appendix A.2):
 // the power of i from multiplying the Pauli (x1,z1) into (x2,z2), per bit in {-1, 0, +1}.
 __device__ __forceinline__ int gsum(uint64_t x1, uint64_t z1, uint64_t x2, uint64_t z2)
@@ -184,6 +163,15 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane)
         if (lane >= d) incl += o;
     }
     return incl - v;
+}
+
+// Block barrier that orders LDS accesses only: global loads and stores may stay in flight across it
+// (__syncthreads waits for them all, which undoes a prefetch issued before it).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // v is the same in every lane (the compiler cannot see that for values read from LDS): keeping

@@ -84,11 +84,16 @@ __device__ __forceinline__ uint64_t uni64(uint64_t v)
 // ------------------------------------------------------------------------------------------
 constexpr int kOneWave = 1024;
 
-struct PlanLds {
-    int k[64 * kWinChunks], piv[64 * kWinChunks], key[2][16], cnt[16], dense, nrun, hits;
-    int pidx[64];                                       // the chunk's pivots: index in the row list, -1: none
-    uint64_t slot[2][16], pw[64];                       // and their words of the chunk at their steps
+// Of one chunk's elimination.
+struct ChunkLds {
+    int key[2][16], pidx[64], hits;                     // pidx: the pivots, as indices in the row list (-1: none)
+    uint64_t slot[2][16], pw[64];                       // pw: their words of the chunk at their steps
     uint64_t unit[64], uhit[64];                        // what the units end with; the steps that hit them
+};
+
+struct PlanLds {
+    int k[64 * kWinChunks], piv[64 * kWinChunks], cnt[16], dense, nrun;
+    ChunkLds c;
     uint64_t pm[64 * kWinChunks][kWinChunks], hit[64 * kWinChunks];
 };
 
@@ -145,7 +150,7 @@ __device__ __forceinline__ int plan_begin(const Geom& g, PlanLds& L, int K, cons
         if (np > start) atomicMax(ran, win + 1);
         L.dense = 0;
         L.nrun = 0;
-        L.hits = 0;
+        L.c.hits = 0;
     }
     __syncthreads();
     return np - start;
@@ -154,7 +159,7 @@ __device__ __forceinline__ int plan_begin(const Geom& g, PlanLds& L, int K, cons
 // The elimination of one chunk on its mask words by one wave; row i of the list is lane i % 64's
 // w[i / 64].
 template <int R>
-__device__ __forceinline__ void chunk_steps_wave(PlanLds& L, uint64_t* Mc, const uint16_t* act, int na, int nt)
+__device__ __forceinline__ void chunk_steps_wave(ChunkLds& L, uint64_t* Mc, const uint16_t* act, int na, int nt)
 {
     const int lane = threadIdx.x & 63;
     uint32_t w[R][2];
@@ -240,16 +245,17 @@ __device__ __forceinline__ void chunk_steps_wave(PlanLds& L, uint64_t* Mc, const
     if (lane == 0) L.hits += hits;
 }
 
-// The same by the whole block, row i of the list being thread i % 1024's w[i / 1024] (16 waves).
+// The same by a block of 64 NW threads, row i of the list being thread i % (64 NW)'s w[i / (64 NW)].
 // Each wave offers its first row with the bit in a slot of its own and takes the lowest offer;
 // the slots alternate between two sets, so a wave that runs ahead writes the set nobody reads.
-template <int R>
-__device__ __forceinline__ void chunk_steps_block(PlanLds& L, uint64_t* Mc, const uint16_t* act, int na, int nt)
+template <int R, int NW>
+__device__ __forceinline__ void chunk_steps_block(ChunkLds& L, uint64_t* Mc, const uint16_t* act, int na, int nt)
 {
+    constexpr int NT = 64 * NW;
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     uint64_t w[R];
 #pragma unroll
-    for (int u = 0; u < R; ++u) w[u] = u * 1024 + tid < na ? Mc[act[u * 1024 + tid]] : 0ull;
+    for (int u = 0; u < R; ++u) w[u] = u * NT + tid < na ? Mc[act[u * NT + tid]] : 0ull;
     uint64_t un = lane < nt ? 1ull << lane : 0ull, hist = 0ull;   // (wave 0's are kept)
     int hits = 0;
 #pragma unroll
@@ -265,18 +271,18 @@ __device__ __forceinline__ void chunk_steps_block(PlanLds& L, uint64_t* Mc, cons
             for (int u = R - 1; u >= 0; --u) {
                 hb[u] = ((uint32_t)(w[u] >> (32 * h)) & bit) != 0u;
                 bm[u] = __ballot(hb[u]);
-                if (bm[u]) first = u * 1024 + wave * 64 + ctz64(bm[u]);
+                if (bm[u]) first = u * NT + wave * 64 + ctz64(bm[u]);
             }
             if (lane == 0) L.key[buf][wave] = first;
 #pragma unroll
             for (int u = 0; u < R; ++u)
-                if (first == u * 1024 + tid) L.slot[buf][wave] = w[u];
+                if (first == u * NT + tid) L.slot[buf][wave] = w[u];
             __syncthreads();
-            int pi = L.key[buf][lane & 15];
+            int pi = (lane & 15) < NW ? L.key[buf][lane & 15] : INT_MAX;
 #pragma unroll
             for (int d = 1; d <= 8; d <<= 1) pi = min(pi, (int)lane_xor32((uint32_t)pi, d, lane));
             pi = uni(pi);
-            const uint64_t pw = pi == INT_MAX ? 0ull : L.slot[buf][(pi >> 6) & 15];
+            const uint64_t pw = pi == INT_MAX ? 0ull : L.slot[buf][(pi >> 6) & (NW - 1)];
             if (tid == 0) {
                 L.pidx[32 * h + j] = pi == INT_MAX ? -1 : pi;
                 L.pw[32 * h + j] = pw;
@@ -297,7 +303,7 @@ __device__ __forceinline__ void chunk_steps_block(PlanLds& L, uint64_t* Mc, cons
     }
 #pragma unroll
     for (int u = 0; u < R; ++u)
-        if (u * 1024 + tid < na) Mc[act[u * 1024 + tid]] = w[u];
+        if (u * NT + tid < na) Mc[act[u * NT + tid]] = w[u];
     if (wave == 0) {
         L.unit[lane] = un;
         L.uhit[lane] = hist;
@@ -366,7 +372,7 @@ __device__ __forceinline__ void plan_end(PlanLds& L, int K, int* cls, const Rand
         count_add(counters, 0, 1ull);
         if (L.dense) count_add(counters, 1, 1ull);
         count_add(counters, 4, (unsigned long long)L.nrun);
-        count_add(counters, 5, (unsigned long long)(L.hits - L.nrun));
+        count_add(counters, 5, (unsigned long long)(L.c.hits - L.nrun));
     }
 }
 
@@ -458,8 +464,8 @@ k_plan(Geom g, const uint64_t* __restrict__ Xcol, int K, int* __restrict__ cls, 
         }
         if (lane == 0) L.cnt[wave] = mine;
         if (tid < 64) {
-            L.pidx[tid] = -1;
-            L.unit[tid] = L.uhit[tid] = 0ull;
+            L.c.pidx[tid] = -1;
+            L.c.unit[tid] = L.c.uhit[tid] = 0ull;
         }
         __syncthreads();
         const int2 pc = wave_counts(L.cnt, nw, wave, lane);
@@ -476,30 +482,30 @@ k_plan(Geom g, const uint64_t* __restrict__ Xcol, int K, int* __restrict__ cls, 
         if (na <= kOneWave) {
             if (wave == 0 && na > 0) {
                 uint64_t* Mc = M + (size_t)c * cap;
-                if (na <= 64) chunk_steps_wave<1>(L, Mc, act, na, nt);
-                else if (na <= 128) chunk_steps_wave<2>(L, Mc, act, na, nt);
-                else if (na <= 256) chunk_steps_wave<4>(L, Mc, act, na, nt);
-                else chunk_steps_wave<kOneWave / 64>(L, Mc, act, na, nt);
+                if (na <= 64) chunk_steps_wave<1>(L.c, Mc, act, na, nt);
+                else if (na <= 128) chunk_steps_wave<2>(L.c, Mc, act, na, nt);
+                else if (na <= 256) chunk_steps_wave<4>(L.c, Mc, act, na, nt);
+                else chunk_steps_wave<kOneWave / 64>(L.c, Mc, act, na, nt);
             }
         } else if (na <= 4096) {
-            chunk_steps_block<4>(L, M + (size_t)c * cap, act, na, nt);
+            chunk_steps_block<4, 16>(L.c, M + (size_t)c * cap, act, na, nt);
         } else {
-            chunk_steps_block<kMaxBands / 16>(L, M + (size_t)c * cap, act, na, nt);
+            chunk_steps_block<kMaxBands / 16, 16>(L.c, M + (size_t)c * cap, act, na, nt);
         }
         __syncthreads();
         for (int t = tid; t < nt; t += nthr) {
-            const int pi = L.pidx[t];
+            const int pi = L.c.pidx[t];
             const uint64_t runm = __ballot(pi >= 0);       // (t = lane: 64 threads, one wave, take it)
             const int row = pi >= 0 ? act[pi] : 0;
-            int later = pi >= 0 ? __popcll(L.pw[t] & (t < 63 ? ~0ull << (t + 1) : 0ull)) : 0;
+            int later = pi >= 0 ? __popcll(L.c.pw[t] & (t < 63 ? ~0ull << (t + 1) : 0ull)) : 0;
 #pragma unroll
             for (int w = 0; w < TW; ++w) {
                 uint64_t v = pi >= 0 && w != c && w < nch ? M[w * cap + row] : 0ull;
                 if (w > c) later += __popcll(v);
-                if (w == c) v = L.unit[t] & runm;
+                if (w == c) v = L.c.unit[t] & runm;
                 L.pm[64 * c + t][w] = v;
             }
-            L.hit[64 * c + t] = L.uhit[t];
+            L.hit[64 * c + t] = L.c.uhit[t];
             L.piv[64 * c + t] = pi >= 0 ? (int)rid[row] : -1;
             if (later > kListCap) L.dense = 1;
             if (t == 0) L.nrun += __popcll(runm);

@@ -563,9 +563,7 @@ int srv_batch_step(stab_server* s, int* nfin)
         A.seed = 0;
         A.err = s->d_err;
         A.counters = s->d_counters;
-        const size_t lds = (size_t)batch_lds_words(maxwc) * 8;
-        if (maxwc <= 64) k_batch<1, 4><<<nc, kBatchThreads, lds, s->stream>>>(A);
-        else k_batch<2, 4><<<nc, kBatchThreads, lds, s->stream>>>(A);
+        batch_start(A, nc, maxwc, 0, s->stream);
         SHIP_CHECK(s, hipGetLastError());
         int err = 0;
         SHIP_CHECK(s, hipMemcpyAsync(&err, s->d_err, sizeof(int), hipMemcpyDeviceToHost, s->stream));
@@ -673,8 +671,10 @@ int stab_server_create(void* dev_buf, uint64_t buf_bytes, void* hip_stream, stab
     s->bytes = (size_t)buf_bytes & ~(size_t)255;
     s->max_lds = lds;
     s->arena.reset(s->bytes);
-    (void)hipFuncSetAttribute((const void*)k_batch<1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_batch<2, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<1, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<2, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<1, 16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute((const void*)k_batch<2, 16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipGetLastError();
     bool ok = hipMalloc((void**)&s->d_err, sizeof(int)) == hipSuccess &&
               hipMalloc((void**)&s->d_counters, kNumCounters * kCounterStripes * sizeof(unsigned long long)) == hipSuccess &&
@@ -724,7 +724,7 @@ int stab_server_program(stab_server* s, const stab_instr* instrs, int32_t ninstr
     if (s->poisoned) return fail(STAB_EDEVICE, "server poisoned by an earlier device error");
     if (n < 1 || ninstr < 0 || ntargets < 0) return fail(STAB_EINVAL, "bad sizes");
     if ((n + 63) / 64 > kBatchMaxWc) return fail(STAB_ERANGE, "more qubits than a batch supports");
-    if (batch_lds_words((n + 63) / 64) * 8 > s->max_lds) return fail(STAB_ERANGE, "circuit too large for LDS");
+    if (batch_lds_words((n + 63) / 64, kBatchWavesMax) * 8 > s->max_lds) return fail(STAB_ERANGE, "circuit too large for LDS");
     if ((ninstr > 0 && !instrs) || (ntargets > 0 && !targets)) return fail(STAB_EINVAL, "null stream");
     SrvProgram P;
     P.n = n;
