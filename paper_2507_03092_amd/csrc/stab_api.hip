@@ -42,13 +42,33 @@ constexpr int kMaxShots = 65535;          // grid y dimension of the reset kerne
 constexpr int kNumKernels = 10;           // timing ids (include/stab.h)
 
 // 32-bit words of the segment kernel's LDS for one half-band (before the per-shot accumulators)
-int seg_lds_words(int RS) { return 64 * (RS + 1) + kRedWords; }
+int seg_lds_words(int Wc) { return 128 * seg_pairs(Wc) + kRedWords; }
+
+// The segment kernel for n qubits: a list's first PF * 1024 entries (events, or two gates) are loaded ahead, which
+// holds any layer of CX gates up to n = 4096 with one (each load costs 16 waves an issue, used or
+// not).
+decltype(&k_segment<false, 1>) segment_kernel(int n, int lds_rd)
+{
+    if (n <= 4 * kSegThreads) return lds_rd ? k_segment<true, 1> : k_segment<false, 1>;
+    return lds_rd ? k_segment<true, 2> : k_segment<false, 2>;
+}
+
+// How many of nitems descriptors to keep in LDS (adding their bytes to lds): as many as leave the
+// blocks of a compute unit as they are.
+int seg_items_lds(int nitems, int max_lds, size_t& lds)
+{
+    const size_t at = (lds + 15) & ~(size_t)15, lim = lds <= (size_t)max_lds / 2 ? max_lds / 2 : max_lds;
+    if (at >= lim) return 0;
+    const int n = (int)std::min<size_t>((size_t)std::min(nitems, 64), (lim - at) / 16);
+    lds = at + (size_t)n * 16;
+    return n;
+}
 
 int max_qubits_for_lds(int lds_bytes)
 {
-    // a staged half-band, 64 * (2*Wc + 1) + kRedWords 32-bit words, must fit
-    const int words = lds_bytes / 4 - kRedWords;
-    const int wc = (words / 64 - 1) / 2;
+    // a staged half-band must fit
+    int wc = kMaxBands;
+    while (wc > 0 && seg_lds_words(wc) * 4 > lds_bytes) --wc;
     // register-resident limits: column words per lane (deterministic wave), stabilizer bands per
     // thread of k_plan
     return std::min(std::min(wc, 64 * kMaxWordsPerLane), kMaxBands) * 64;
@@ -148,7 +168,6 @@ struct SegPlan {
     long long ev_cap = 0;
     long long ev_global = 0;   // first event slot of the segment when the whole program is drawn at once
     int meas = -1;
-    long long gate_count = 0;
 };
 
 struct MeasPlan {
@@ -177,7 +196,7 @@ struct stab_program {
     void* dev = nullptr;
     bool dev_arena = false;   // dev lies in the static scratch (stab_sample_noalloc)
     int4* d_items = nullptr;
-    uint2* d_gates = nullptr;
+    uint32_t* d_gates = nullptr;
     NoiseDesc* d_noise = nullptr;
     int* d_noise_tg = nullptr;
     int* d_unit_start = nullptr;
@@ -193,6 +212,7 @@ struct stab_program {
     std::vector<int> mran;
     bool mran_known = false;
     int* d_mtq = nullptr;
+    long long ngates = 0;
     // geometry it was compiled for
     int n = 0, B = 0;
     uint64_t serial = 0;   // distinct for every program of the process (keys captured graphs)
@@ -375,32 +395,45 @@ RandBufs rand_bufs(const RandLayout& L, void* p)
 // measurement layers (disjoint qubits); see the file header.
 int compile_stream(const Geom& g, const stab_instr* ins, int ninstr, const int32_t* tg,
                    int64_t ntg, stab_program& P, std::vector<int4>& items,
-                   std::vector<uint2>& gates, std::vector<NoiseDesc>& noise,
+                   std::vector<uint32_t>& gates, std::vector<NoiseDesc>& noise,
                    std::vector<int>& noise_tg, std::vector<int>& unit_start,
                    std::vector<int>& ev_base, std::vector<int>& mtq)
 {
     if (ninstr < 0 || ntg < 0) return fail(STAB_EINVAL, "negative count");
     if ((ninstr > 0 && !ins) || (ntg > 0 && !tg)) return fail(STAB_EINVAL, "null stream");
     const int n = g.n;
-    // gate and noise targets are stored as the word index of the qubit's column in the segment
-    // kernel's staged tile, (q mod 64) * (RS + 1) + q / 64
-    const uint32_t RSP = (uint32_t)g.RS + 1u;
-    auto tile_index = [&](int q) { return (uint32_t)(q & 63) * RSP + (uint32_t)(q >> 6); };
+    // gate and noise targets are stored as the qubit's pair in the segment kernel's staged tile
+    auto tile_index = [&](int q) { return (uint32_t)((q & 63) * seg_pairs(g.Wc) + (q >> 6)); };
     std::vector<int> stamp(n, -1), mstamp(n, -1);
     int layer_id = 0, mlayer_id = 0;
     SegPlan seg;
-    int open_begin = -1;
     long long rec_off = 0;
 
+    // the open layer's gates by kind, in the order of the segment kernel's items (SegArgs)
+    std::vector<uint32_t> open[6], all;
+    auto add_gate = [&](uint32_t kind, int q, int q1) {
+        const int at = kind == STAB_CX ? 0 : (int)(kind - STAB_H) + 1;
+        open[at].push_back(tile_index(q) | tile_index(q1) << 16);
+    };
     auto close_layer = [&]() {
-        if (open_begin >= 0) {
-            const int cnt = (int)gates.size() - open_begin;
-            if (cnt > 0) {
-                items.push_back(make_int4(0, open_begin, cnt, -1));
-                seg.item_count++;
-                seg.gate_count += cnt;
-            }
-            open_begin = -1;
+        const int begin = (int)gates.size();
+        int c[6];
+        all.clear();
+        for (int k = 0; k < 6; ++k) {
+            c[k] = (int)open[k].size();
+            all.insert(all.end(), open[k].begin(), open[k].end());
+            open[k].clear();
+        }
+        const int cnt = (int)all.size(), half = (cnt + 1) / 2;
+        for (int k = 0; k < half; ++k) {
+            gates.push_back(all[k]);
+            gates.push_back(k + half < cnt ? all[k + half] : 0u);
+        }
+        P.ngates += cnt;
+        if (cnt > 0) {
+            items.push_back(make_int4(c[3] << 1 | c[4] << (1 + kGateBits), begin, cnt | c[2] << kGateBits,
+                                      c[0] | c[1] << kGateBits));
+            seg.item_count++;
         }
         ++layer_id;
     };
@@ -438,9 +471,8 @@ int compile_stream(const Geom& g, const stab_instr* ins, int ninstr, const int32
         case STAB_H: case STAB_S: case STAB_X: case STAB_Y: case STAB_Z:
             for (uint32_t q = 0; q < nt; ++q) {
                 if (stamp[t[q]] == layer_id) close_layer();
-                if (open_begin < 0) open_begin = (int)gates.size();
                 stamp[t[q]] = layer_id;
-                gates.push_back(make_uint2(kind | (tile_index(t[q]) << 4), 0u));
+                add_gate(kind, t[q], t[q]);
                 if (kind == STAB_H || kind == STAB_S) seg.modifies = 1;
             }
             break;
@@ -449,9 +481,8 @@ int compile_stream(const Geom& g, const stab_instr* ins, int ninstr, const int32
                 const int c = t[q], d = t[q + 1];
                 if (c == d) return fail(STAB_EINVAL, "instruction " + std::to_string(k) + ": CX with equal qubits");
                 if (stamp[c] == layer_id || stamp[d] == layer_id) close_layer();
-                if (open_begin < 0) open_begin = (int)gates.size();
                 stamp[c] = stamp[d] = layer_id;
-                gates.push_back(make_uint2(kind | (tile_index(c) << 4), tile_index(d)));
+                add_gate(kind, c, d);
                 seg.modifies = 1;
             }
             break;
@@ -469,7 +500,7 @@ int compile_stream(const Geom& g, const stab_instr* ins, int ninstr, const int32
             d.units = units;
             // noise layers with no gate between them act on the same tableau: they share one
             // event bucket (their events commute) and one item of the segment kernel
-            const bool join = seg.item_count > 0 && items.back().x == 1;
+            const bool join = seg.item_count > 0 && (items.back().x & 1);
             d.bucket = join ? items.back().w : (int)ev_base.size();
             for (uint32_t q = 0; q < nt; ++q) noise_tg.push_back((int)tile_index(t[q]));
             unit_start.push_back(seg.units);
@@ -604,12 +635,14 @@ int create_ctx(int32_t n, int32_t shots, int32_t mode, uint64_t seed, uint64_t f
         return fail(STAB_EDEVICE, "no HIP device");
     }
     ctx->max_lds = lds;
-    const int seg_bytes = seg_lds_words(ctx->g.RS) * 4;
+    const int seg_bytes = seg_lds_words(ctx->g.Wc) * 4;
     if (seg_bytes > lds) {
         delete ctx;
         return fail(STAB_ERANGE, "a half-band of the tableau does not fit in this device's LDS");
     }
-    (void)hipFuncSetAttribute((const void*)k_segment, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    for (int lrd = 0; lrd < 2; ++lrd)
+        for (int q : {1, 64 * kMaxBands})
+            (void)hipFuncSetAttribute((const void*)segment_kernel(q, lrd), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_plan, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
     (void)hipFuncSetAttribute((const void*)k_det<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -718,7 +751,7 @@ int compile_host(const Geom& g, const stab_instr* instrs, int32_t ninstr, const 
                  int64_t ntargets, stab_program& P, ProgramBlob& B)
 {
     std::vector<int4> items;
-    std::vector<uint2> gates;
+    std::vector<uint32_t> gates;
     std::vector<NoiseDesc> noise;
     std::vector<int> noise_tg, unit_start, ev_base, mtq;
     int rc = compile_stream(g, instrs, ninstr, targets, ntargets, P, items, gates, noise, noise_tg,
@@ -764,7 +797,7 @@ int upload_program(stab_ctx* ctx, stab_program& P, const ProgramBlob& B)
     }
     char* d = (char*)P.dev;
     P.d_items = (int4*)(d + B.items);
-    P.d_gates = (uint2*)(d + B.gates);
+    P.d_gates = (uint32_t*)(d + B.gates);
     P.d_noise = (NoiseDesc*)(d + B.noise);
     P.d_noise_tg = (int*)(d + B.ntg);
     P.d_unit_start = (int*)(d + B.us);
@@ -811,17 +844,17 @@ int stab_plan_describe(int32_t n, int32_t shots, int32_t mode, const stab_instr*
     if (rc) return rc;
     stab_program P;
     std::vector<int4> items;
-    std::vector<uint2> gates;
+    std::vector<uint32_t> gates;
     std::vector<NoiseDesc> noise;
     std::vector<int> noise_tg, unit_start, ev_base, mtq;
     rc = compile_stream(make_geom(n, shots, mode), instrs, ninstr, targets, ntargets, P, items, gates, noise,
                         noise_tg, unit_start, ev_base, mtq);
     if (rc) return rc;
     long long gate_layers = 0, units = 0;
-    for (const int4& it : items) gate_layers += it.x == 0 ? 1 : 0;
+    for (const int4& it : items) gate_layers += (it.x & 1) ? 0 : 1;
     for (const NoiseDesc& d : noise) units += d.units;
     const int64_t v[STAB_PLAN_FIELDS] = {(int64_t)P.segs.size(), (int64_t)P.meas.size(), gate_layers,
-                                         (int64_t)gates.size(), (int64_t)noise.size(), units, P.nrec, P.Kmax};
+                                         P.ngates, (int64_t)noise.size(), units, P.nrec, P.Kmax};
     for (int i = 0; i < nout; ++i) out[i] = v[i];
     return STAB_OK;
 }
@@ -892,9 +925,9 @@ int exec_lds(const Geom& g, int max_lds, ExecLds* out)
     ExecLds E;
     // per-shot sign accumulators in LDS only where they keep two half-band blocks per compute
     // unit (or where even one block without them would not get two)
-    const int seg_base = seg_lds_words(g.RS) * 4, seg_acc = (seg_lds_words(g.RS) + g.bpc) * 4;
+    const int seg_base = seg_lds_words(g.Wc) * 4, seg_acc = (seg_lds_words(g.Wc) + g.bpc) * 4;
     E.lds_rd = (seg_acc <= max_lds / 2 || (seg_base > max_lds / 2 && seg_acc <= max_lds)) ? 1 : 0;
-    E.seg_lds = (size_t)(seg_lds_words(g.RS) + (E.lds_rd ? g.bpc : 0)) * 4;
+    E.seg_lds = (size_t)(seg_lds_words(g.Wc) + (E.lds_rd ? g.bpc : 0)) * 4;
     *out = E;
     return STAB_OK;
 }
@@ -925,8 +958,6 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
     ExecLds E;
     int rc = exec_lds(g, ctx->max_lds, &E);
     if (rc) return rc;
-    const int lds_rd = E.lds_rd;
-    const size_t seg_lds = E.seg_lds;
     int* ran = (int*)ctx->ran.p;
     const RandLayout RL = rand_layout(g, P->Kmax);
     const RandBufs R = rand_bufs(RL, ctx->rnd.p);
@@ -965,7 +996,8 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
                 a.ev_count = P->d_ev_count;
                 a.ev_base = P->d_ev_base;
                 a.write_back = sp.modifies;
-                a.lds_rd = lds_rd;
+                size_t lds = E.seg_lds;
+                a.nlds = seg_items_lds(sp.item_count, ctx->max_lds, lds);
                 if (sp.meas >= 0) {
                     const MeasPlan& m = P->meas[sp.meas];
                     a.ext_q = P->d_mtq + m.tq_begin;
@@ -976,7 +1008,7 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
                 }
                 a.Xcol = Xcol;
                 a.Zcol = Zcol;
-                TIMED(ctx, 2, (k_segment<<<dim3(2 * g.NB, g.S), kSegThreads, seg_lds, ctx->stream>>>(
+                TIMED(ctx, 2, (segment_kernel(g.n, E.lds_rd)<<<dim3(2 * g.NB, g.S), kSegThreads, lds, ctx->stream>>>(
                                   g, ctx->tab, ctx->rs, ctx->rd, a)));
             }
         } else {
@@ -1027,13 +1059,12 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
                 a.ev_count = P->d_ev_count;
                 a.ev_base = P->d_ev_base;
                 a.write_back = 0;
-                a.lds_rd = 0;
                 a.ext_q = P->d_mtq + m.tq_begin;
                 a.K = K2;
                 a.Xcol = Xcol;
                 a.Zcol = Zcol;
                 a.gate = ran;
-                TIMED(ctx, 9, (k_segment<<<dim3(2 * g.NB, g.S), kSegThreads, (size_t)seg_lds_words(g.RS) * 4,
+                TIMED(ctx, 9, (k_segment<false, 1><<<dim3(2 * g.NB, g.S), kSegThreads, (size_t)seg_lds_words(g.Wc) * 4,
                                            ctx->stream>>>(g, ctx->tab, ctx->rs, ctx->rd, a)));
             }
             // targets found deterministic within the layer: reduced in parallel on the final tableau

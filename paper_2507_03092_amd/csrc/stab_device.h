@@ -48,15 +48,22 @@ __device__ __forceinline__ void count_add(unsigned long long* counters, int idx,
     if (counters) atomicAdd(&counters[idx * kCounterStripes + (blockIdx.x & (kCounterStripes - 1))], v);
 }
 
+// Gates of a layer: at most a qubit each.
+constexpr int kGateBits = 14, kGateMask = (1 << kGateBits) - 1;
+static_assert(64 * kMaxBands <= kGateMask, "gate counts of an item");
+
 struct SegArgs {
-    const int4* items;     // {0, first gate, gate count, -1} or {1, first event slot, event capacity, bucket}
+    // {0 | Xs << 1 | Ys << 15, first gate, gate count | Ss << 14, CXs | Hs << 14} or {1, first event slot,
+    // event capacity, bucket}
+    const int4* items;
     int nitems;
-    const uint2* gates;    // {kind | i0 << 4, i1}, i = the qubit's word index in the staged tile
-    const uint2* events;   // noise events {tile word index of the qubit | pauli << 28, shot}
+    int nlds;              // items whose descriptors the kernel keeps in LDS (past the sign accumulators)
+    const uint32_t* gates; // i0 | i1 << 16, i = the qubit's pair in the staged tile (i1 = i0 for one qubit);
+                           // an item's gates 0, h, 1, h + 1, ... with h = half of them, rounded up
+    const uint2* events;   // noise events {tile pair of the qubit | pauli << 28, shot}
     const int* ev_count;   // per bucket
     const int* ev_base;    // per bucket: first slot in events
     int write_back;        // 1 if some gate changes x|z (H, S, CX)
-    int lds_rd;            // 1: accumulate per-shot signs in LDS (bpc fits)
     const int* ext_q;      // qubits whose columns the next measurement layer needs
     int K;
     uint64_t* Xcol;        // [S][NB][K]

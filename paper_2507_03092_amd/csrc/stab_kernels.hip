@@ -280,83 +280,117 @@ k_noise_draw(const NoiseDesc* __restrict__ nd, const int* __restrict__ ntg, int 
 }
 
 // ------------------------------------------------------------------------------------------
-// Segment kernel helpers.  Column j of a staged half-band: x word at
-// T[(j & 63) * RSP + (j >> 6)], z word at + Wc (32-bit words, one bit per staged row).
+// Segment kernel helpers.
 // ------------------------------------------------------------------------------------------
-constexpr int kSegPrefetch = 5;   // gates / events per thread prefetched into registers
+// The staged tile: the x and z words of qubit q's 32 rows are the pair at (q & 63) * seg_pairs(Wc) +
+// (q >> 6) (an odd stride, so consecutive qubits fall on different banks).
+__host__ __device__ constexpr int seg_pairs(int Wc) { return Wc | 1; }
 
-// Registers holding one item's gate or noise-event list (first kSegPrefetch * blockDim.x).
+// Descriptor of an item of a segment, a gate layer (its gates sorted by kind: CX, H, S, X, Y, Z) or a
+// noise layer, as in SegArgs::items with a noise item's count resolved.
+__device__ __forceinline__ int4 seg_item(const SegArgs& a, const int4* items, int it)
+{
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    typedef const v4i __attribute__((address_space(4)))* Int4s;
+    typedef const int __attribute__((address_space(4)))* Ints;
+    if (it >= a.nitems) return make_int4(0, 0, 0, 0);
+    if (it < a.nlds) return items[it];
+    const v4i v = *((Int4s)a.items + it);
+    return make_int4(v.x, v.y, (v.x & 1) ? *((Ints)a.ev_count + v.w) : v.z, v.w);
+}
+
+// Registers holding the first PF * blockDim.x entries of an item's list: noise events, or two gates
+// each (entry k has gates k and k + half), so that both take the same loads.
+template <int PF>
 struct ItemBuf {
-    uint2 v[kSegPrefetch];
-    int count;     // units in the item
-    int type;      // 0 gates, 1 noise, -1 none
-    const uint2* src;
+    uint2 v[PF];
+    int x, y, z, w;   // the item
+    __device__ bool noise() const { return x & 1; }
+    __device__ int gates() const { return z & kGateMask; }
+    __device__ int entries() const { return (x & 1) ? z : (gates() + 1) >> 1; }
 };
 
-__device__ __forceinline__ void fetch_item(const SegArgs& a, int it, int tid, int nt, ItemBuf& b)
+// Wait for a load here, so that no path leaves the loop with it pending (the next items' lists would
+// then be waited for with it).
+__device__ __forceinline__ void landed(uint2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
+// Loads past the list's end are bounded by the buffer descriptor (they return 0): every thread issues
+// the same loads whatever the item, so the wait for one item's leaves a later one's in flight.
+template <int PF>
+__device__ __forceinline__ void fetch_item(const SegArgs& a, int4 d, int tid, int nt, ItemBuf<PF>& b)
 {
-    if (it >= a.nitems) {
-        b.type = -1;
-        b.count = 0;
-        return;
-    }
-    const int4 item = a.items[it];
-    b.type = item.x;
-    // gates: count known; events: the bucket's slots are read up to its capacity while its
-    // count is loaded (both in flight at once), and the count bounds their use
-    b.src = item.x == 0 ? a.gates + item.y : a.events + item.y;
-    b.count = item.x == 0 ? item.z : a.ev_count[item.w];
+    b.x = uni(d.x);
+    b.y = uni(d.y);
+    b.z = uni(d.z);
+    b.w = uni(d.w);
+    const void* list = b.noise() ? (const void*)(a.events + b.y) : (const void*)(a.gates + b.y);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)list, (short)0, b.entries() * 8, 0x00027000);
 #pragma unroll
-    for (int u = 0; u < kSegPrefetch; ++u) {
-        const int i = tid + u * nt;
-        if (i < item.z) b.v[u] = b.src[i];
+    for (int u = 0; u < PF; ++u) {
+        const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (tid + u * nt) * 8, 0, 0);
+        b.v[u] = make_uint2(t[0], t[1]);
     }
 }
 
-// A gate on the 32 staged rows: x word of qubit q at T[(q & 63) * RSP + (q >> 6)], z at + Wc;
-// the gate list holds these word indices (resolved on the host).
-__device__ __forceinline__ void apply_gate(uint32_t* T, int Wc, uint2 gt, uint32_t& racc)
+// Gates i and i + n of a layer of count gates (x, z, w as in SegArgs::items) on the 32 staged rows; gt:
+// the tile pairs of their qubits (0 past the end), w0: i of the wave's first thread.  All four pairs
+// are read before any is written (a layer's qubits are distinct).  A wave of CX gates only runs
+// those; else every kind runs the same instructions, by masks: with the second qubit equal to the
+// first, H and S are a CX's sign rule x0 z1 (x1 ^ z0 ^ 1) = x0 z0 with another update.
+__device__ __forceinline__ void apply_gates(uint2* T, uint2 gt, int i, int w0, int n, int count, int x, int z, int w,
+                                            uint32_t& racc)
 {
-    const int kind = (int)(gt.x & 15u);
-    const int i0 = (int)(gt.x >> 4);
-    const uint32_t x0 = T[i0], z0 = T[i0 + Wc];
-    switch (kind) {
-    case STAB_KIND_H:
-        racc ^= x0 & z0;
-        T[i0] = z0;
-        T[i0 + Wc] = x0;
-        break;
-    case STAB_KIND_S:
-        racc ^= x0 & z0;
-        T[i0 + Wc] = z0 ^ x0;
-        break;
-    case STAB_KIND_X: racc ^= z0; break;
-    case STAB_KIND_Y: racc ^= x0 ^ z0; break;
-    case STAB_KIND_Z: racc ^= x0; break;
-    case STAB_KIND_CX: {
-        const int i1 = (int)gt.y;
-        const uint32_t x1 = T[i1], z1 = T[i1 + Wc];
-        racc ^= x0 & z1 & ~(x1 ^ z0);
-        T[i1] = x1 ^ x0;
-        T[i0 + Wc] = z0 ^ z1;
-    } break;
-    default: break;
+    const int c0 = w & kGateMask;
+    uint2* t[2][2] = {{T + (gt.x & 0xFFFFu), T + (gt.x >> 16)}, {T + (gt.y & 0xFFFFu), T + (gt.y >> 16)}};
+    uint2 q[2][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        q[e][0] = *t[e][0];
+        q[e][1] = *t[e][1];
+    }
+    const bool on[2] = {i < n, i + n < count};
+    if (min(w0 + n + 64, count) <= c0) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint2 a = q[e][0], b = q[e][1];
+            if (on[e]) {
+                racc ^= a.x & b.y & ~(b.x ^ a.y);
+                t[e][1]->x = b.x ^ a.x;
+                t[e][0]->y = a.y ^ b.y;
+            }
+        }
+    } else {
+        const int c1 = c0 + (w >> kGateBits), c2 = c1 + (z >> kGateBits), c3 = c2 + (x >> 1 & kGateMask),
+                  c4 = c3 + (x >> (1 + kGateBits));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            auto below = [&](int c) { return (uint32_t)((i + e * n - c) >> 31); };
+            const uint2 a = q[e][0], b = q[e][1];
+            const uint32_t u = below(c2), cx = below(c0), hs = u & ~cx, h = below(c1) & hs;
+            const uint32_t r = (a.x & b.y & ~(b.x ^ a.y) & u) ^ (a.x & ~below(c3)) ^ (a.y & below(c4) & ~u);
+            if (on[e]) {
+                racc ^= r;
+                t[e][1]->x = b.x ^ (a.x & cx) ^ ((a.x ^ a.y) & h);
+                t[e][0]->y = a.y ^ (b.y & cx) ^ (a.x & hs) ^ (a.y & h);
+            }
+        }
     }
 }
 
-// Noise event {tile word index of the qubit | pauli << 28, shot}: flip the signs of the rows the
-// Pauli anticommutes with.
-__device__ __forceinline__ void apply_event(const uint32_t* T, int Wc, uint2 v, int s, int hb,
-                                            const Geom& g, const SegArgs& a, uint32_t* rdacc,
+// Noise event {tile pair of the qubit | pauli << 28, shot}: flip the signs of the rows the Pauli
+// anticommutes with.  LRD: per-shot signs in LDS (a choice at run time would make the atomic a flat
+// one, which waits for every load in flight).
+template <bool LRD>
+__device__ __forceinline__ void apply_event(const uint2* T, uint2 v, int s, int hb, const Geom& g, uint32_t* rdacc,
                                             uint32_t* rd32)
 {
     const int sb = (int)v.y - s * g.bpc;
     if (sb < 0 || sb >= g.bpc) return;
-    const int iq = (int)(v.x & 0x0FFFFFFFu), P = (int)(v.x >> 28);
-    const uint32_t xq = T[iq], zq = T[iq + Wc];
-    const uint32_t m = (P == 1) ? zq : (P == 3) ? xq : (xq ^ zq);
+    const uint2 q = T[v.x & 0x0FFFFFFFu];
+    const int P = (int)(v.x >> 28);
+    const uint32_t m = (P == 1) ? q.y : (P == 3) ? q.x : (q.x ^ q.y);
     if (m) {
-        if (a.lds_rd) atomicXor(&rdacc[sb], m);
+        if (LRD) atomicXor(&rdacc[sb], m);
         else atomicXor(&rd32[(size_t)(s * g.bpc + sb) * 2 * g.NB + hb], m);
     }
 }
@@ -380,38 +414,65 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane)
     return v;
 }
 
-// Transpose every 32x32 tile (column c of the 64 staged lanes) in place, four tiles per wave in
-// flight so that their LDS reads overlap.  A wave's pair of tiles that is all zero (most of a
-// sparse tableau, such as a surface code's) is its own transpose and is left as it is.
-__device__ __forceinline__ void transpose_tiles(uint32_t* T, int RSP, int RS, int lane, int wave, int nwaves)
+// Transpose of 32x32 bit matrices held by lane pairs (lane, lane + 32): lane q * 32 + j has rows
+// 16q .. 16q + 15 of pair j's matrix in w, and gets the same rows of its transpose.  One exchange
+// between the two lanes, then four stages among a lane's own words: 160 instructions for 32
+// matrices, where a row per lane takes 25 for two (transpose32).  Every lane must be active.
+__device__ __forceinline__ void transpose32_pairs(uint32_t (&w)[16], int lane)
 {
-    int c = wave;
-    for (; c + 3 * nwaves < RS; c += 4 * nwaves) {
-        uint32_t v[4];
+    const uint32_t sel = lane < 32 ? 0x05040100u : 0x07060302u;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = T[lane * RSP + c + u * nwaves];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (__ballot(v[u] != 0u)) {
-                v[u] = transpose32(v[u], lane);
-                T[lane * RSP + c + u * nwaves] = v[u];
-            }
-        }
+    for (int i = 0; i < 16; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false);
+        w[i] = __builtin_amdgcn_perm(r[1], r[0], sel);
     }
-    for (; c < RS; c += nwaves) {
-        const uint32_t v = T[lane * RSP + c];
-        if (__ballot(v != 0u)) T[lane * RSP + c] = transpose32(v, lane);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t a = w[i], b = w[i + 8];
+        w[i] = __builtin_amdgcn_perm(b, a, 0x06020400u);
+        w[i + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);
+    }
+    const uint32_t masks[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+    for (int st = 0; st < 3; ++st) {
+        const int j = 4 >> st;
+        const uint32_t m = masks[st];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (i & j) continue;
+            const uint32_t a = w[i], b = w[i + j];
+            w[i] = (a & m) | ((b << j) & ~m);
+            w[i + j] = ((a >> j) & m) | (b & ~m);
+        }
     }
 }
 
+// Whether any lane has a bit set; an all-zero set of matrices (most of a sparse tableau, such as a
+// surface code's) is its own transpose.
+__device__ __forceinline__ bool any_bit(const uint32_t (&w)[16])
+{
+    uint32_t o = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o |= w[i];
+    return __ballot(o != 0u) != 0ull;
+}
+
 // ------------------------------------------------------------------------------------------
-// Segment kernel: grid (2 * NB half-bands, S copies), 1024 threads.  A block stages 32 rows
-// (half of a 64-row band) as 32-bit qubit-major words: row r's 64-bit word c is split into
-// its low half (columns 64c..64c+31, staged at lane r) and high half (lane 32 + r); each
-// half-wave then transposes its 32x32 tile, so afterwards lane L of tile c holds column
-// 64c + L for the 32 rows.  Two such blocks fit the LDS of one compute unit.  The block owns
-// the 32-bit half of every sign word and column-extract word of its band.
+// Segment kernel: grid (2 * NB half-bands, S copies), 1024 threads.  A block holds 32 rows (half of
+// a 64-row band) in LDS as 32-bit qubit-major words, a qubit's x and z bits of the rows side by side
+// (seg_pairs).  Two such blocks fit the LDS of one compute unit up to 10176 qubits.  The
+// rows are transposed on the way, in registers: a wave's lane pairs load the 32 words of 32
+// columns (32 rows of 32 bits each), and write the transposed words; the way back is the same.
+// The block owns the 32-bit half of every sign word and column-extract word of its band.
+//
+// It is bound by the chain from layer to layer, not by bytes (632 blocks of a 10081-qubit tableau
+// move 102 MB in 50 us): per layer the list's load, four LDS reads and two writes a gate, and a
+// barrier.  So lists are loaded two layers ahead across barriers that order LDS only, gates take 4
+// bytes and two of a thread run together, and the descriptors lie in LDS.  Launches of a memory
+// round at d = 25 (1249 qubits, 100 shots) 13.5 -> 12.0 us, at d = 71 57 -> 50 us, 40 copies of
+// d = 25 95 -> 86 us.
 // ------------------------------------------------------------------------------------------
+template <bool LRD, int PF>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
 k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
           uint64_t* __restrict__ rd, SegArgs a)
@@ -422,69 +483,92 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
     const int band = hb >> 1, half = hb & 1;
     const int s = blk_y(g);
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6, nwaves = nt >> 6;
-    const int RS = g.RS, RSP = g.RS + 1, Wc = g.Wc;
-    uint32_t* T = lds32;                         // 64 x RSP
-    uint32_t* red = lds32 + 64 * RSP;            // nwaves words
-    uint32_t* rdacc = red + 16;                  // bpc words when a.lds_rd
+    const int lane = tid & 63, wave = uni(tid >> 6), nwaves = nt >> 6;
+    const int RS = g.RS, Wc = g.Wc, RP = seg_pairs(Wc);
+    uint2* T = (uint2*)lds32;                    // 64 x RP pairs
+    uint32_t* red = lds32 + 128 * RP;            // nwaves words
+    uint32_t* rdacc = red + 16;                  // bpc words when LRD
+    int4* items = (int4*)(lds32 + ((128 * RP + 16 + (LRD ? g.bpc : 0) + 3) & ~3));   // nlds descriptors
     uint64_t* gb = tab + ((size_t)s * 2 * g.NR + (size_t)band * 64 + (size_t)half * 32) * RS;
     uint32_t* rs32 = (uint32_t*)rs;
     uint32_t* rd32 = (uint32_t*)rd;
 
-    ItemBuf cur, nxt;
-    fetch_item(a, 0, tid, nt, cur);
-
-    // 32 rows -> LDS with 16-byte loads (RS is even, so a pair never crosses a row), 4 in
-    // flight; word (r, c) splits into T[r][c] (low half) and T[32 + r][c] (high half)
-    const int npairs = 16 * RS;
-    const ulonglong2* gb2 = (const ulonglong2*)gb;
-    for (int p0 = 0; p0 < npairs; p0 += 4 * nt) {
-        ulonglong2 v[4];
+    for (int it = tid; it < a.nlds; it += nt) {
+        int4 v = a.items[it];
+        if (v.x & 1) v.z = a.ev_count[v.w];
+        items[it] = v;
+    }
+    // columns j of 32 bits, two lanes each; rows 16 (lane >> 5) .. + 15 and, transposed, the
+    // column's bits of the same numbers
+    const int ncol = 2 * RS, q16 = (lane >> 5) * 16;
+    uint32_t* gr = (uint32_t*)gb + (size_t)q16 * ncol;
+    for (int j0 = wave * 32; j0 < ncol; j0 += nwaves * 32) {
+        const int j = j0 + (lane & 31);
+        uint32_t w[16];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int p = p0 + u * nt + tid;
-            if (p < npairs) v[u] = gb2[p];
-        }
+        for (int r = 0; r < 16; ++r) w[r] = j < ncol ? gr[r * ncol + j] : 0u;
+        if (any_bit(w)) transpose32_pairs(w, lane);
+        const int c = j >> 1, comp = c >= Wc;
+        uint32_t* t = lds32 + ((32 * (j & 1) + q16) * RP + c - comp * Wc) * 2 + comp;
+        if (j < ncol) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int p = p0 + u * nt + tid;
-            if (p < npairs) {
-                const int i = 2 * p;
-                const int r = i / RS;
-                const int c = i - r * RS;
-                uint32_t* lo = T + r * RSP + c;
-                uint32_t* hi = lo + 32 * RSP;
-                lo[0] = (uint32_t)v[u].x;
-                lo[1] = (uint32_t)v[u].y;
-                hi[0] = (uint32_t)(v[u].x >> 32);
-                hi[1] = (uint32_t)(v[u].y >> 32);
-            }
+            for (int b = 0; b < 16; ++b) t[2 * b * RP] = w[b];
         }
     }
-    if (a.lds_rd)
+    if (LRD)
         for (int b = tid; b < g.bpc; b += nt) rdacc[b] = 0;
-    __syncthreads();
-    transpose_tiles(T, RSP, RS, lane, wave, nwaves);
     __syncthreads();
 
     uint32_t racc = 0;
-    for (int it = 0; it < a.nitems; ++it) {
-        fetch_item(a, it + 1, tid, nt, nxt);       // next item's list, in flight meanwhile
-        if (cur.type == 0) {
+    // item it's list is loaded two items ahead, into one of three buffers (no register moves: a move
+    // would wait for the load), and its descriptor three
+    ItemBuf<PF> b0, b1, b2;
+    int4 desc = make_int4(0, 0, 0, 0);
+    if (a.nitems > 0) {
+        fetch_item(a, seg_item(a, items, 0), tid, nt, b0);
+        fetch_item(a, seg_item(a, items, 1), tid, nt, b1);
+        desc = seg_item(a, items, 2);
+    }
+    auto step = [&](const ItemBuf<PF>& cur, ItemBuf<PF>& next, int it) {
+        fetch_item(a, desc, tid, nt, next);
+        desc = seg_item(a, items, it + 3);
+        const int w0 = wave * 64, n = cur.entries();
+        if (!cur.noise()) {
+            const uint2* list = (const uint2*)(a.gates + cur.y);
+            const int count = cur.gates();
+            auto gates = [&](uint2 gt, int k) {
+                apply_gates(T, gt, tid + k, w0 + k, n, count, cur.x, cur.z, cur.w, racc);
+            };
 #pragma unroll
-            for (int u = 0; u < kSegPrefetch; ++u)
-                if (tid + u * nt < cur.count) apply_gate(T, Wc, cur.v[u], racc);
-            for (int gi = tid + kSegPrefetch * nt; gi < cur.count; gi += nt)
-                apply_gate(T, Wc, cur.src[gi], racc);
+            for (int u = 0; u < PF; ++u)
+                if (w0 + u * nt < n) gates(cur.v[u], u * nt);
+            for (int k = PF * nt; w0 + k < n; k += nt) {
+                uint2 gt = list[min(tid + k, n - 1)];
+                landed(gt);
+                gates(gt, k);
+            }
         } else {
+            const uint2* list = a.events + cur.y;
 #pragma unroll
-            for (int u = 0; u < kSegPrefetch; ++u)
-                if (tid + u * nt < cur.count) apply_event(T, Wc, cur.v[u], s, 2 * band + half, g, a, rdacc, rd32);
-            for (int e = tid + kSegPrefetch * nt; e < cur.count; e += nt)
-                apply_event(T, Wc, cur.src[e], s, 2 * band + half, g, a, rdacc, rd32);
+            for (int u = 0; u < PF; ++u)
+                if (tid + u * nt < n) apply_event<LRD>(T, cur.v[u], s, 2 * band + half, g, rdacc, rd32);
+            for (int e0 = tid + PF * nt; e0 < n; e0 += 4 * nt) {
+                uint2 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = list[min(e0 + u * nt, n - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) landed(v[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (e0 + u * nt < n) apply_event<LRD>(T, v[u], s, 2 * band + half, g, rdacc, rd32);
+            }
         }
-        __syncthreads();
-        cur = nxt;
+        lds_barrier();
+    };
+    for (int it = 0; it < a.nitems; it += 3) {
+        step(b0, b2, it);
+        if (it + 1 < a.nitems) step(b1, b0, it + 1);
+        if (it + 2 < a.nitems) step(b2, b1, it + 2);
     }
 
     if (a.K > 0) {
@@ -492,26 +576,24 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
         uint32_t* Zc = (uint32_t*)(a.Zcol + ((size_t)s * g.NB + band) * a.K);
         for (int k = tid; k < a.K; k += nt) {
             const int q = a.ext_q[k];
-            const int iq = (q & 63) * RSP + (q >> 6);
-            Xc[2 * k + half] = T[iq];
-            Zc[2 * k + half] = T[iq + Wc];
+            const uint2 t = T[(q & 63) * RP + (q >> 6)];
+            Xc[2 * k + half] = t.x;
+            Zc[2 * k + half] = t.y;
         }
     }
     if (a.write_back) {
-        __syncthreads();
-        transpose_tiles(T, RSP, RS, lane, wave, nwaves);
-        __syncthreads();
-        ulonglong2* gw2 = (ulonglong2*)gb;
-        for (int p = tid; p < npairs; p += nt) {
-            const int i = 2 * p;
-            const int r = i / RS;
-            const int c = i - r * RS;
-            const uint32_t* lo = T + r * RSP + c;
-            const uint32_t* hi = lo + 32 * RSP;
-            ulonglong2 v;
-            v.x = (uint64_t)lo[0] | ((uint64_t)hi[0] << 32);
-            v.y = (uint64_t)lo[1] | ((uint64_t)hi[1] << 32);
-            gw2[p] = v;
+        for (int j0 = wave * 32; j0 < ncol; j0 += nwaves * 32) {
+            const int j = j0 + (lane & 31);
+            const int c = j >> 1, comp = c >= Wc;
+            const uint32_t* t = lds32 + ((32 * (j & 1) + q16) * RP + c - comp * Wc) * 2 + comp;
+            uint32_t w[16];
+#pragma unroll
+            for (int b = 0; b < 16; ++b) w[b] = j < ncol ? t[2 * b * RP] : 0u;
+            if (any_bit(w)) transpose32_pairs(w, lane);
+            if (j < ncol) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) gr[r * ncol + j] = w[r];
+            }
         }
     }
     // sign contributions: XOR-reduce 32-bit masks
@@ -524,7 +606,7 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
         for (int w = 0; w < nwaves; ++w) t ^= red[w];
         if (t) rs32[((size_t)s * g.NB + band) * 2 + half] ^= t;
     }
-    if (a.lds_rd) {
+    if (LRD) {
         for (int b = tid; b < g.bpc; b += nt) {
             const uint32_t v = rdacc[b];
             if (v) rd32[((size_t)(s * g.bpc + b) * g.NB + band) * 2 + half] ^= v;
