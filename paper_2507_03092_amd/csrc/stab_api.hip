@@ -1397,10 +1397,13 @@ extern "C" int stab_commute(const uint64_t* A, int32_t na, const uint64_t* B, in
         return fail(STAB_EINVAL, "arrays must be 8-byte aligned");
     if (na == 0 || nb == 0) return STAB_OK;
     const int W = (n + 63) / 64;
-    const long long rows = ((long long)na + kCommRows - 1) / kCommRows;
-    if (rows > 65535) return fail(STAB_ERANGE, "too many strings in A (at most 65535 * 64)");
-    const dim3 grid((unsigned)((nb + 63) / 64), (unsigned)rows);
-    k_commute<<<grid, kCommThreads, 0, (hipStream_t)hip_stream>>>(A, na, B, nb, W, gc, qwc);
+    if (((long long)na + 63) / 64 > 65535) return fail(STAB_ERANGE, "too many strings in A (at most 65535 * 64)");
+    // words a block walks over: up to kCommRowWords, as many as leave 1024 blocks
+    const long long rows = ((long long)na + kCommRows - 1) / kCommRows, nbw = ((long long)nb + 63) / 64;
+    const int words = (int)std::max(1ll, std::min((long long)kCommRowWords, rows * nbw / 1024));
+    const dim3 grid((unsigned)((nbw + words - 1) / words), (unsigned)rows);
+    (W <= kCommWords ? k_commute<true> : k_commute<false>)<<<grid, kCommThreads, 0, (hipStream_t)hip_stream>>>(
+        A, na, B, nb, W, words, gc, qwc);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(STAB_EDEVICE, std::string("k_commute: ") + hipGetErrorString(e));
     return STAB_OK;
