@@ -277,7 +277,9 @@ __device__ __noinline__ void batch_segment(ArgsPtr ap, int ci_, int st_, int en_
     while (nbd < kBatchBands && nbd < NB && batch_tile_words(RS, nbd + 1) <= room) ++nbd;
     nbd = uni(nbd);
     uint64_t* sacc = lds + nbd * 64 * RSP;         // sign flips per band
-    int4* steps = (int4*)((uintptr_t)(sacc + NB + 1) & ~(uintptr_t)15);
+    // (an index, not an aligned address: that would make its accesses flat ones, which wait for every
+    // load in flight: 45.7 -> 44.5 ms for 100 shots of the 1249-qubit circuit)
+    int4* steps = (int4*)(lds + ((nbd * 64 * RSP + NB + 1) & ~1));
     int* off = (int*)(steps + kBatchSteps);        // noise step i's events: [off[i], off[i + 1])
     uint32_t* evs = (uint32_t*)off + kBatchNoiseSteps + 2;
     uint64_t* tab = A.tab + C.tab_off;
