@@ -38,9 +38,8 @@ DEFAULTS = {  # steps, warmup, shots (circuits) timed in the plain form
     "serve": (1, 0, 0),
 }
 COMMUTE_METRIC = "Pauli-string pairs/sec, group-wise and qubit-wise commutation matrices, bit-exact"
-# int32 VALU operations per second: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (the fp32 vector
-# figure of 157.3 TFLOP/s counts a fused multiply-add as two and packs two fp32 per lane)
-VALU_INT32_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# matrix-core operations per second in fp4: 256 CUs x 4 SIMDs x 4096 a cycle x 2.4 GHz
+FP4_PEAK_TOPS = 256 * 4 * 4096 * 2.4e9 / 1e12     # dense, 2 x 32 x 32 x 64 in 32 cycles a SIMD
 BATCH_METRIC = "measurements/sec of an uneven multi-circuit batch (random Clifford circuits), bit-exact"
 
 
@@ -107,10 +106,10 @@ def surface_alg_bytes(n, d, rounds, shots, mode, work, per_step) -> dict:
         # data readout; K = d*d-1 ancillas, then d*d data qubits
         "segment": rounds * seg_bytes_per_launch(n, shots, mode, d * d - 1, True)
         + seg_bytes_per_launch(n, shots, mode, d * d, False),
-        # per random measurement: the stabilizer half of its column, the pivot row read, logged
-        # and replaced; per stabilizer rowsum row a read and a write
-        "chain": work[4] * (wc * 8 + 3 * row_b) + work[5] * 2 * row_b,
-        # per walked destabilizer a read and a write, per applied pivot its logged row read
+        # per random measurement (windows: k_plan, k_snap): the stabilizer half of its column, its
+        # masks, the pivot row read and kept
+        "chain": work[4] * (wc * 8 + 64 + 2 * row_b),
+        # (k_apply) per changed row a read and a write, per destabilizer rowsum a pivot row read
         "replay": work[9] * 2 * row_b + work[8] * row_b,
         # the final tableau read and the columns of every target written (about d*d targets)
         "extract": per_step.get("extract", (0, 0))[1] * seg_bytes_per_launch(n, shots, mode, d * d, False),
@@ -784,12 +783,12 @@ def bench_commute(args) -> int:
     ms_step = (t1 - t0) * 1000.0 / steps
     pairs = float(m) * m
     W = (n + 63) // 64
-    ops = pairs * W * 10          # per pair and 64-bit word: 2 AND, 3 XOR/OR on 32-bit halves x 2
+    ops = pairs * W * 64 * 3 * 2  # per pair and qubit: three products and sums
     achieved = ops / (k_ms / 1000.0) / 1e12
     log(f"commute: {ms_step:.3f} ms/step, kernel {k_ms:.3f} ms, {pairs / (ms_step / 1000.0):.4e} pairs/s")
-    roofline = {"kernel": "commute", "bound": "alu", "achieved": round(achieved, 2),
-                "peak": round(VALU_INT32_PEAK_TOPS, 2), "unit": "Tops/s (int32 VALU)",
-                "frac": round(achieved / VALU_INT32_PEAK_TOPS, 4), "traffic": None,
+    roofline = {"kernel": "commute", "bound": "mfma", "achieved": round(achieved, 2),
+                "peak": round(FP4_PEAK_TOPS, 2), "unit": "Tops/s (fp4 MFMA)",
+                "frac": round(achieved / FP4_PEAK_TOPS, 4), "traffic": None,
                 "ops_per_launch": int(ops), "avg_launch_us": round(k_ms * 1000.0, 2)}
     cpu = None
     if not args.no_cpu_baseline:

@@ -187,7 +187,7 @@ int stab_sample(const stab_instr *instrs, int32_t ninstr, const int32_t *targets
  * Same arguments, semantics and out_bits layout as stab_sample (no elapsed time).  The
  * caller still provides the tableaux (dev_buf, stab_tableau_bytes bytes) and the host output;
  * every buffer stab_sample would allocate (error flag, counters, the uploaded program, target
- * columns, noise events, pivot log, records) is carved instead from one static device array of
+ * columns, noise events, window buffers, records) is carved instead from one static device array of
  * STAB_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until the process ends.
  * Nothing is allocated or freed on the device: no hipMalloc, hipFree, event or stream creation
  * (host-side the stream is compiled in ordinary heap memory, as by stab_sample).  Noise is drawn
