@@ -244,6 +244,21 @@ __device__ __forceinline__ void batch_noise(const NoiseDesc& d, const int* __res
     }
 }
 
+// A list filled step by step by a whole block: append(i) adds step i's entries at slots counted up in
+// *count, and off[i + 1] becomes the end of step i's.  The end is read between two barriers: without
+// the second, a thread already in step i + 1 could count entries of its own into step i's.
+template <class Append, class Barrier>
+__host__ __device__ __forceinline__ void list_by_step(int nsteps, int tid, int* off, const int* count, Append append,
+                                                      Barrier barrier)
+{
+    for (int i = 0; i < nsteps; ++i) {
+        append(i);
+        barrier();
+        if (tid == 0) off[i + 1] = *count;
+        barrier();
+    }
+}
+
 // One run of gate/noise steps [st, en) over every band of the circuit.
 // With ncol > 0, the band pass also writes the x and z columns of targets tq[sel[k]] (tq[k] with sel
 // = kNoSel; tq: their start in the target array), k < ncol, 64 rows per word, to the circuit's
@@ -326,20 +341,19 @@ __device__ __noinline__ void batch_segment(ArgsPtr ap, int ci_, int st_, int en_
         int* nev = off + kBatchNoiseSteps + 1;
         if (tid == 0) off[0] = *nev = 0;
         __syncthreads();
-        for (int k = st, i = 0; k < en; ++k) {
-            const int4 s = A.steps[k];
-            if (s.x == 0) continue;
-            const NoiseDesc d = A.noise[s.y];
-            for (int u = tid; u < d.units; u += nt)
-                batch_noise(d, A.noise_tg, u, key, ibase, [&](int q, int P) {
-                    const int e = atomicAdd(nev, 1);
-                    if (e < kBatchNoiseEvents) evs[e] = (uint32_t)((q & 63) * RSP + (q >> 6)) | (uint32_t)P << 28;
-                });
-            __syncthreads();
-            if (tid == 0) off[i + 1] = *nev;
-            ++i;
-        }
-        __syncthreads();
+        int k = st;
+        list_by_step(
+            nn, tid, off, nev,
+            [&](int) {
+                while (A.steps[k].x == 0) ++k;
+                const NoiseDesc d = A.noise[A.steps[k++].y];
+                for (int u = tid; u < d.units; u += nt)
+                    batch_noise(d, A.noise_tg, u, key, ibase, [&](int q, int P) {
+                        const int e = atomicAdd(nev, 1);
+                        if (e < kBatchNoiseEvents) evs[e] = (uint32_t)((q & 63) * RSP + (q >> 6)) | (uint32_t)P << 28;
+                    });
+            },
+            [] { __syncthreads(); });
         listed = uni(off[nn]) <= kBatchNoiseEvents;
     }
     const int TS = 64 * RSP;                       // words between the bands' tiles
