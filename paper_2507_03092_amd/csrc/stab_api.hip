@@ -345,7 +345,7 @@ RandLayout rand_layout(const Geom& g, int Kmax)
 {
     RandLayout L{};
     L.Tc = std::min(64 * kWinChunks, std::max(Kmax, 1));
-    L.multi = Kmax > L.Tc;
+    L.multi = Kmax > least_window(g);
     const size_t ST = (size_t)g.S * L.Tc;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -961,7 +961,7 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
     int* ran = (int*)ctx->ran.p;
     const RandLayout RL = rand_layout(g, P->Kmax);
     const RandBufs R = rand_bufs(RL, ctx->rnd.p);
-    const bool wide = g.NR > kPlanRows;
+    const int least = std::min(R.Tc, least_window(g));
     const int plan_threads = 64 * std::min(16, g.Wr), plan_lds = plan_lds_bytes(g.NR);
     const int aw = (g.Wc + 63) / 64;                      // k_apply's words per lane
     const int apply_thr = apply_threads(aw);
@@ -1024,8 +1024,7 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
             // would return at once; otherwise that execution's count of windows is known
             const int known = use_mran ? P->mran[st.second] : -1;
             if (known != 0) {
-            // (above n = 4096 a window can be cut to 64 targets)
-            int nwin = known > 0 ? known : (K2 + (wide ? 64 : R.Tc) - 1) / (wide ? std::min(64, R.Tc) : R.Tc);
+            const int nwin = known > 0 ? known : (K2 + least - 1) / least;
             const bool ask = known < 0 && may_sync && nwin > kMaxBlindWindows;
             int until = ask ? 1 : nwin;
             const Snap snap{ctx->tab, ctx->rs, ctx->rd, obuf, ctx->seed, ctx->first_shot, base + m.instr, m.pos_base,

@@ -39,13 +39,16 @@ constexpr int kWinChunks = 4;       // 64-target chunks of a window
 // first 64 targets, one word a row.
 constexpr int kPlanRows = 4096;
 
+// Targets of a window that is not the layer's last, at least.
+__host__ __device__ inline int least_window(const Geom& g) { return g.NR > kPlanRows ? 64 : 64 * kWinChunks; }
+
 // Scratch of the random measurements (per copy s; Tc = min(64 kWinChunks, the program's largest layer)).
 struct RandBufs {
     int4* win;        // [S] {pending targets of the layer, the window's first, how many, 0}; the count
                       // carries kDenseFlag if a pivot has x at more than kListCap later targets
     int* piv;         // [S][Tc] stabilizer index of the target's pivot, -1: deterministic by then
     int* cw;          // [S][Tc] i-exponent of the snapshot: |x & z| + 2 * shared sign (mod 4)
-    int* dirty;       // [S][NB] quarters of the band changed in this layer (NULL: one window at most)
+    int* dirty;       // [S][NB] quarters of the band changed in this layer (NULL: a layer takes one window at most)
     uint64_t* pm;     // [S][Tc][kWinChunks] of target t: in its own chunk's word, what unit t ends
                       // that chunk with (pivots of the chunk); in the others, its pivot's mask at
                       // the start of the chunk

@@ -46,12 +46,28 @@ static void check_list_by_step()
     }
 }
 
+// A layer that may take more than one window has the array of changed quarter bands: more targets
+// than a window holds, or rows k_plan may have to cut a window for.
+static void check_windows_of_a_layer()
+{
+    for (int n : {1, 64, 300, 4096, 4097, 4160, 10240})
+        for (int K : {1, 63, 64, 65, 130, 256, 257, 4096}) {
+            if (K > n) continue;
+            const Geom g = make_geom(n, 3, STAB_MODE_SHARED);
+            const int least = g.NR > kPlanRows ? 64 : 64 * kWinChunks;   // targets of the smallest window but the last
+            const RandLayout L = rand_layout(g, K);
+            EXPECT(L.multi == (K > least), "n %d, %d targets: multi %d", n, K, (int)L.multi);
+            EXPECT((rand_bufs(L, (void*)256).dirty != nullptr) == (K > least), "n %d, %d targets: dirty", n, K);
+            EXPECT(L.pm - L.dirty >= (K > least ? (size_t)g.S * g.NB * 4 : 0), "n %d, %d targets: size", n, K);
+        }
+}
+
 int main(int argc, char** argv)
 {
     const struct {
         const char* name;
         void (*run)();
-    } checks[] = {{"list_by_step", check_list_by_step}};
+    } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer}};
     for (const auto& c : checks)
         if (argc == 2 && !std::strcmp(argv[1], c.name)) {
             c.run();
