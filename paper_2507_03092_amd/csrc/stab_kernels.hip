@@ -314,6 +314,10 @@ struct ItemBuf {
 // then be waited for with it).
 __device__ __forceinline__ void landed(uint2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 
+// Bytes of a list of `entries` that the descriptor of its first `ahead` covers (the whole list's would
+// not fit 32 bits from 2^29 entries on).
+__host__ __device__ constexpr int ahead_bytes(int entries, int ahead) { return (entries < ahead ? entries : ahead) * 8; }
+
 // Loads past the list's end are bounded by the buffer descriptor (they return 0): every thread issues
 // the same loads whatever the item, so the wait for one item's leaves a later one's in flight.
 template <int PF>
@@ -324,7 +328,7 @@ __device__ __forceinline__ void fetch_item(const SegArgs& a, int4 d, int tid, in
     b.z = uni(d.z);
     b.w = uni(d.w);
     const void* list = b.noise() ? (const void*)(a.events + b.y) : (const void*)(a.gates + b.y);
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)list, (short)0, b.entries() * 8, 0x00027000);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)list, (short)0, ahead_bytes(b.entries(), PF * nt), 0x00027000);
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
         const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (tid + u * nt) * 8, 0, 0);
@@ -552,15 +556,16 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
 #pragma unroll
             for (int u = 0; u < PF; ++u)
                 if (tid + u * nt < n) apply_event<LRD>(T, cur.v[u], s, 2 * band + half, g, rdacc, rd32);
-            for (int e0 = tid + PF * nt; e0 < n; e0 += 4 * nt) {
+            // (unsigned: up to 2^31 - 1 events)
+            for (uint32_t e0 = tid + PF * nt; e0 < (uint32_t)n; e0 += 4 * nt) {
                 uint2 v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = list[min(e0 + u * nt, n - 1)];
+                for (int u = 0; u < 4; ++u) v[u] = list[min(e0 + u * nt, (uint32_t)n - 1)];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) landed(v[u]);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (e0 + u * nt < n) apply_event<LRD>(T, v[u], s, 2 * band + half, g, rdacc, rd32);
+                    if (e0 + u * nt < (uint32_t)n) apply_event<LRD>(T, v[u], s, 2 * band + half, g, rdacc, rd32);
             }
         }
         lds_barrier();

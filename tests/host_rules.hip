@@ -62,12 +62,23 @@ static void check_windows_of_a_layer()
         }
 }
 
+// The part of a noise list that a segment loads ahead, up to the most events a segment may have.
+static void check_list_ahead()
+{
+    for (int ahead : {1024, 2048})
+        for (int n : {0, 1, 1023, 1024, 1025, 2048, 1 << 20, (1 << 28) - 1, 1 << 28, 1 << 29, (1 << 29) + 5, 1 << 30, INT_MAX}) {
+            const int got = ahead_bytes(n, ahead), want = 8 * std::min(n, ahead);
+            EXPECT(got == want, "%d entries, %d ahead: %d bytes, not %d", n, ahead, got, want);
+        }
+}
+
 int main(int argc, char** argv)
 {
     const struct {
         const char* name;
         void (*run)();
-    } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer}};
+    } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer},
+                  {"list_ahead", check_list_ahead}};
     for (const auto& c : checks)
         if (argc == 2 && !std::strcmp(argv[1], c.name)) {
             c.run();
