@@ -230,8 +230,9 @@ int stab_set_timing(stab_ctx *ctx, int32_t kernel_mask);
  * packing) into a hipGraph the first time it runs it, and replays the graph while the program,
  * the RNG seed and first shot, the instruction counter and the context's buffers are the same
  * as at capture (a program executed right after stab_reset, again and again, replays); any
- * other execution captures anew.  Results are those of the eager launches.  The record copy
- * to the host and the consistency check stay outside the graph.  Errors: STAB_EINVAL (null
+ * other execution captures anew, or runs eagerly where it starts away from |0...0> and a layer
+ * measures more than 256 qubits (64 above 4096 qubits).  Results are those of the eager launches.
+ * The record copy to the host and the consistency check stay outside the graph.  Errors: STAB_EINVAL (null
  * context). */
 int stab_set_graph(stab_ctx *ctx, int32_t enable);
 int stab_get_kernel_times(stab_ctx *ctx, double *ms, uint64_t *launches, int32_t nkernels);

@@ -381,6 +381,12 @@ RandBufs rand_bufs(const RandLayout& L, void* p)
     return R;
 }
 
+// Whether an execution may be captured: its launches are few or their number is known.  Away from
+// |0...0> the windows of a layer are not known, and a captured layer has to hold every possible one
+// (237 launches a layer at d = 71, where an eager execution asks how many are pending); such an
+// execution is captured anew each time at any rate, the instruction counter being another.
+bool captures(const Geom& g, int Kmax, bool known) { return known || Kmax <= least_window(g); }
+
 #define TIMED(ctx, kind, ...)                    \
     do {                                         \
         int rc_ = tstart(ctx, kind);             \
@@ -1112,7 +1118,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
     };
 
     if (ctx->ev0) HIP_CHECK(ctx, hipEventRecord(ctx->ev0, ctx->stream));
-    if (ctx->graph_on && !ctx->timing && !learn_mran) {
+    if (ctx->graph_on && !ctx->timing && !learn_mran && captures(g, P->Kmax, use_mran)) {
         // the launches depend on the program, the RNG key, the instruction counter and the
         // buffers: replay the captured graph while they are unchanged, capture again otherwise
         uint64_t bufsig = 0;

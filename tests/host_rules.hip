@@ -72,13 +72,26 @@ static void check_list_ahead()
         }
 }
 
+// A captured layer holds three launches a window: as many windows as it takes, known or at most one.
+static void check_captures()
+{
+    for (int n : {300, 4096, 4097, 10081})
+        for (int K : {1, 64, 65, 256, 257, 5040}) {
+            if (K > n) continue;
+            const Geom g = make_geom(n, 10, STAB_MODE_SHARED);
+            EXPECT(captures(g, K, true), "n %d, %d targets: windows known", n, K);
+            EXPECT(captures(g, K, false) == !rand_layout(g, K).multi, "n %d, %d targets: windows unknown", n, K);
+        }
+}
+
 int main(int argc, char** argv)
 {
     const struct {
         const char* name;
         void (*run)();
     } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer},
-                  {"list_ahead", check_list_ahead}};
+                  {"list_ahead", check_list_ahead},
+                  {"captures", check_captures}};
     for (const auto& c : checks)
         if (argc == 2 && !std::strcmp(argv[1], c.name)) {
             c.run();
