@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -140,6 +141,8 @@ struct stab_ctx {
     unsigned long long* d_counters = nullptr;
     DevBuf xcol, zcol, cls, obuf, events, record, packed, pend, ran;
     DevBuf rnd;                   // scratch of the random measurements (RandBufs)
+    uint64_t* post = nullptr;     // pinned word k_plan answers in (allocated when first asked)
+    uint32_t post_seq = 0;        // k_plan launches that were to answer
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     // per-kernel timing (stab_set_timing)
     bool timing = false;
@@ -649,7 +652,8 @@ int create_ctx(int32_t n, int32_t shots, int32_t mode, uint64_t seed, uint64_t f
     for (int lrd = 0; lrd < 2; ++lrd)
         for (int q : {1, 64 * kMaxBands})
             (void)hipFuncSetAttribute((const void*)segment_kernel(q, lrd), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_plan, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
+    (void)hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
+    (void)hipFuncSetAttribute((const void*)k_plan<false>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
     (void)hipFuncSetAttribute((const void*)k_det<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<3>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -705,6 +709,7 @@ void stab_destroy(stab_ctx* ctx)
                       &ctx->events, &ctx->record, &ctx->packed, &ctx->pend, &ctx->ran, &ctx->rnd};
     for (DevBuf* b : bufs)
         if (b->p && !b->arena) (void)hipFree(b->p);
+    if (ctx->post) (void)hipHostFree(ctx->post);
     if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
     if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
@@ -938,18 +943,49 @@ int exec_lds(const Geom& g, int max_lds, ExecLds* out)
     return STAB_OK;
 }
 
+// targets of a window (one word of shots) up to which k_plan's waves take the snapshots, two each,
+// which saves a launch
+constexpr int kFusedSnaps = 32;
+// windows launched without knowing the pending targets (reading the count back costs about as much
+// as ten launches that return at once)
+constexpr int kMaxBlindWindows = 4;
+
+// The pending targets left by the last launched window, from the word that k_plan answers in or,
+// without one (the context allocates nothing), from the window's descriptor on the device.  Reading
+// back idles the device for 32 to 36 us a layer: 30 rounds of a d = 33 memory that goes on from
+// another state take 3.12 ms that way and 2.15 ms with the word, a first execution at d = 45 5.32 and
+// 3.72 ms (2.66 and 4.90 with the targets one after another in one launch).
+int windows_left(stab_ctx* ctx, const RandBufs& R, int* left)
+{
+    if (!ctx->post) {
+        int v[4] = {0, 0, 0, 0};   // the first copy's (the same in all)
+        HIP_CHECK(ctx, hipMemcpyAsync(v, R.win, 16, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
+        *left = v[0] - v[1] - (v[2] & ~kDenseFlag);
+        return STAB_OK;
+    }
+    auto answered = [&](uint64_t v) { return (uint32_t)(v >> 32) == ctx->post_seq; };
+    uint64_t v = 0;
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    for (int i = 0; !answered(v = __atomic_load_n(ctx->post, __ATOMIC_ACQUIRE)); ++i) {
+        __builtin_ia32_pause();
+        if ((i & 255) == 255 && std::chrono::steady_clock::now() > until) {
+            // a long way behind (or in error): wait for the stream
+            HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
+            if (answered(v = __atomic_load_n(ctx->post, __ATOMIC_ACQUIRE))) break;
+            ctx->poisoned = true;
+            return fail(STAB_EINTERNAL, "no count of pending targets");
+        }
+    }
+    *left = (int)(uint32_t)v;
+    return STAB_OK;
+}
+
 // Every launch of one execution of P on ctx->stream, eagerly or into a graph (a fill kernel
 // clears the event counts: no memset node in a captured graph).  use_mran skips the launches of
 // measurement layers where nothing ran in an earlier execution from |0...0>; learn_mran writes,
 // in P->d_mran, how many windows of random targets each layer took.  may_sync: the caller allows
 // waiting for the stream (not while capturing, nor in the server).
-// targets of a window (one word of shots) up to which k_plan's waves take the snapshots, two each,
-// which saves a launch
-constexpr int kFusedSnaps = 32;
-// windows launched without knowing the pending targets (waiting for the count costs about as much
-// as ten launches that return at once)
-constexpr int kMaxBlindWindows = 4;
-
 int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, bool learn_mran, bool may_sync)
 {
     const Geom& g = ctx->g;
@@ -1033,21 +1069,25 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
             const int nwin = known > 0 ? known : (K2 + least - 1) / least;
             const bool ask = known < 0 && may_sync && nwin > kMaxBlindWindows;
             int until = ask ? 1 : nwin;
+            if (ask && !ctx->post && !ctx->arena) {
+                if (hipHostMalloc((void**)&ctx->post, sizeof(uint64_t), hipHostMallocCoherent) == hipSuccess) *ctx->post = 0;
+                else ctx->post = nullptr, (void)hipGetLastError();
+            }
             const Snap snap{ctx->tab, ctx->rs, ctx->rd, obuf, ctx->seed, ctx->first_shot, base + m.instr, m.pos_base,
-                            g.bpc <= 64 && std::min(R.Tc, K2) <= kFusedSnaps};
+                      g.bpc <= 64 && std::min(R.Tc, K2) <= kFusedSnaps};
+            uint64_t* post = ask ? ctx->post : nullptr;
             for (int w = 0; w < nwin; ++w) {
                 if (w == until) {
-                    // many windows that may all be empty: read how many targets are left
-                    int v[4] = {0, 0, 0, 0};   // the first copy's (the same in all)
-                    HIP_CHECK(ctx, hipMemcpyAsync(v, R.win, 16, hipMemcpyDeviceToHost, ctx->stream));
-                    HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
-                    const int left = v[0] - v[1] - (v[2] & ~kDenseFlag);
+                    // many windows that may all be empty: ask how many targets are left
+                    int left = 0;
+                    if ((rc = windows_left(ctx, R, &left))) return rc;
                     if (left <= 0) break;
                     until = w + (left + R.Tc - 1) / R.Tc;
                 }
                 TIMED(ctx, 5, {
-                    k_plan<<<g.S, plan_threads, plan_lds, ctx->stream>>>(g, Xcol, K2, cls, (int*)ctx->pend.p, R, w,
-                                                                         ran, snap, ctx->d_counters);
+                    (post ? k_plan<true> : k_plan<false>)<<<g.S, plan_threads, plan_lds, ctx->stream>>>(
+                        g, Xcol, K2, cls, (int*)ctx->pend.p, R, w, ran, snap, ctx->d_counters, post,
+                        post ? ++ctx->post_seq : 0u);
                     if (!snap.fused)
                         k_snap<<<dim3(R.Tc, g.S), kSnapThreads, 0, ctx->stream>>>(g, K2, (const int*)ctx->pend.p, snap, R);
                 });

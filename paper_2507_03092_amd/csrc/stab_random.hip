@@ -325,6 +325,15 @@ struct Snap {
     int fused;      // k_plan takes the snapshots
 };
 
+// How many pending targets the window leaves (the first copy's count, the same in all), with the
+// launch's number, to a word of pinned host memory: the host reads it while the window is planned.
+template <bool POST>
+__device__ __forceinline__ void post_left(uint64_t* post, uint32_t seq, int s, int left)
+{
+    if (POST && s == 0 && threadIdx.x == 0)
+        __hip_atomic_store(post, (uint64_t)seq << 32 | (uint32_t)left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The snapshot of target t (index k in its layer, pivot p) by a group of 64 nw threads, wave w of
 // it: row and i-exponent by the first wave, per-shot signs and outcome draws by all.
 __device__ __forceinline__ void snap_target(const Geom& g, const Snap& S, const RandBufs& R, int s, int t, int k, int p,
@@ -386,9 +395,10 @@ __host__ __device__ inline int plan_lds_bytes(int NR)
 }
 static_assert(kPlanRows * (kWinChunks * 8 + 4) >= kMaxBands * 64 * 12, "a cut window's one-word rows must fit");
 
+template <bool POST>
 __global__ void __launch_bounds__(1024)
 k_plan(Geom g, const uint64_t* __restrict__ Xcol, int K, int* __restrict__ cls, int* __restrict__ pend, RandBufs R,
-       int win, int* __restrict__ ran, Snap S, unsigned long long* __restrict__ counters)
+       int win, int* __restrict__ ran, Snap S, unsigned long long* __restrict__ counters, uint64_t* post, uint32_t seq)
 {
     constexpr int TW = kWinChunks;
     extern __shared__ uint64_t M[];                       // [tw][cap] masks
@@ -397,7 +407,10 @@ k_plan(Geom g, const uint64_t* __restrict__ Xcol, int K, int* __restrict__ cls, 
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = uni(tid >> 6), nw = nthr >> 6;
     int start;
     const int left = plan_begin(g, L, K, cls, pend + (size_t)s * K, R, win, ran, s, start);
-    if (left <= 0) return;
+    if (left <= 0) {
+        post_left<POST>(post, seq, s, 0);
+        return;
+    }
     int nwt = min(R.Tc, left), tw = TW, cap = min(g.NR, kPlanRows), n = 0;
     const uint64_t* Xs = Xcol + (size_t)s * g.NB * K + (size_t)g.Wr * K;
     uint16_t *rid, *act;
@@ -455,6 +468,7 @@ k_plan(Geom g, const uint64_t* __restrict__ Xcol, int K, int* __restrict__ cls, 
         tw = 1;
         cap = g.NR;
     }
+    post_left<POST>(post, seq, s, left - nwt);
     const int nch = (nwt + 63) >> 6;
     const int per = (n + nthr - 1) / nthr;                 // 64-row runs of the list a wave takes
     for (int c = 0; c < nch; ++c) {
