@@ -369,7 +369,9 @@ int stab_commute(const uint64_t *A, int32_t na, const uint64_t *B, int32_t nb, i
  *   STAB_LANE_SHARED the request's shots share one x|z tableau (STAB_MODE_SHARED; Pauli noise
  *                    only).  Admission enqueues the request's whole stream on one of the
  *                    server's device streams; requests on different streams overlap on the
- *                    device, and a step retires those that completed.
+ *                    device, and a step retires those that completed.  Where a layer measures
+ *                    more than 256 qubits, a stream's later requests start once its first one has
+ *                    finished.
  *   STAB_LANE_AUTO   (default) SHARED for streams without T1T2 noise, else BATCH.
  * A server is not thread-safe.  Per request it allocates nothing on the device: the shared lane
  * compiles and uploads a stream once per power-of-two shot bucket (at its first request), and
@@ -412,10 +414,11 @@ int stab_server_submit(stab_server *server, int32_t prog, int32_t shots, uint64_
                        int64_t *id_out);
 
 /* Retire shared-lane requests that completed, admit what fits (shared-lane requests start at
- * once), run one batch-lane launch over every resident batch-lane shot and retire the batch-lane
+ * once, or when the first of their stream has finished), run one batch-lane launch over every resident batch-lane shot and retire the batch-lane
  * requests that finished (their records are copied to host memory and their bytes freed).  Waits
- * for the batch launch only.  *finished_out (may be NULL) receives the number of requests that
- * finished. */
+ * for the batch launch, and when a program of more than 4096 qubits with a layer of more than 1024
+ * targets runs in the shared lane for the first time, for the counts of its layers' random targets.
+ * *finished_out (may be NULL) receives the number of requests that finished. */
 int stab_server_step(stab_server *server, int32_t *finished_out);
 
 /* Drop a request: queued, resident (a shared-lane request's launches finish; its bytes are freed

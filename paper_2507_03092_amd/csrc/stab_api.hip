@@ -947,8 +947,10 @@ int exec_lds(const Geom& g, int max_lds, ExecLds* out)
 // which saves a launch
 constexpr int kFusedSnaps = 32;
 // windows launched without knowing the pending targets (reading the count back costs about as much
-// as ten launches that return at once)
-constexpr int kMaxBlindWindows = 4;
+// as ten launches that return at once), and in a server, which serves others meanwhile (41 windows a
+// layer for the first request of a d = 51 memory: 22 ms for a burst of four with all of them launched,
+// 11.9 ms asking, 16.2 with the targets one after another in one launch)
+constexpr int kMaxBlindWindows = 4, kMaxBlindServer = 16;
 
 // The pending targets left by the last launched window, from the word that k_plan answers in or,
 // without one (the context allocates nothing), from the window's descriptor on the device.  Reading
@@ -984,9 +986,9 @@ int windows_left(stab_ctx* ctx, const RandBufs& R, int* left)
 // Every launch of one execution of P on ctx->stream, eagerly or into a graph (a fill kernel
 // clears the event counts: no memset node in a captured graph).  use_mran skips the launches of
 // measurement layers where nothing ran in an earlier execution from |0...0>; learn_mran writes,
-// in P->d_mran, how many windows of random targets each layer took.  may_sync: the caller allows
-// waiting for the stream (not while capturing, nor in the server).
-int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, bool learn_mran, bool may_sync)
+// in P->d_mran, how many windows of random targets each layer took.  A layer that may take more than
+// `blind` windows waits for the count of its pending targets (never while capturing).
+int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, bool learn_mran, int blind)
 {
     const Geom& g = ctx->g;
     uint64_t* Xcol = (uint64_t*)ctx->xcol.p;
@@ -1067,7 +1069,7 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
             const int known = use_mran ? P->mran[st.second] : -1;
             if (known != 0) {
             const int nwin = known > 0 ? known : (K2 + least - 1) / least;
-            const bool ask = known < 0 && may_sync && nwin > kMaxBlindWindows;
+            const bool ask = known < 0 && nwin > blind;
             int until = ask ? 1 : nwin;
             if (ask && !ctx->post && !ctx->arena) {
                 if (hipHostMalloc((void**)&ctx->post, sizeof(uint64_t), hipHostMallocCoherent) == hipSuccess) *ctx->post = 0;
@@ -1153,9 +1155,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
     const uint64_t base = ctx->instr_counter;
     const bool use_mran = base == 0 && P->mran_known;
     const bool learn_mran = base == 0 && !P->mran_known && !P->meas.empty();
-    auto enqueue = [&](bool may_sync) -> int {
-        return exec_enqueue(ctx, P, draw_all, use_mran, learn_mran, may_sync);
-    };
+    auto enqueue = [&](int blind) -> int { return exec_enqueue(ctx, P, draw_all, use_mran, learn_mran, blind); };
 
     if (ctx->ev0) HIP_CHECK(ctx, hipEventRecord(ctx->ev0, ctx->stream));
     if (ctx->graph_on && !ctx->timing && !learn_mran && captures(g, P->Kmax, use_mran)) {
@@ -1175,7 +1175,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
             HIP_CHECK(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
             hipStream_t run_stream = ctx->stream;
             ctx->stream = ctx->cap_stream;          // the launches below are recorded, not run
-            const int erc = enqueue(false);
+            const int erc = enqueue(INT_MAX);
             hipGraph_t gr = nullptr;
             const hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &gr);
             ctx->stream = run_stream;
@@ -1189,7 +1189,7 @@ int stab_execute(stab_ctx* ctx, stab_program* P, uint8_t* out_bits, float* elaps
             std::memcpy(ctx->gkey, key, sizeof(key));
         }
         HIP_CHECK(ctx, hipGraphLaunch(ctx->gexec, ctx->stream));
-    } else if ((rc = enqueue(true))) {
+    } else if ((rc = enqueue(kMaxBlindWindows))) {
         return rc;
     }
     std::vector<uint8_t> host;

@@ -349,13 +349,16 @@ int srv_launch_shared(stab_server* s, SrvRequest& r)
         r.P.mran = G.mran;
         r.P.mran_known = true;
     }
+    char* pin = s->pinned + r.pin_off;
+    const size_t rec_b = (size_t)r.shots * (size_t)((r.P.nrec + 7) / 8);
+    ctx->post = (uint64_t*)(pin + align256(rec_b) + 128);   // (past the error flag)
+    *ctx->post = 0;
     bool draw_all = false;
-    if ((rc = exec_prepare(ctx, &r.P, false, &draw_all)) || (rc = exec_enqueue(ctx, &r.P, draw_all, G.mran_known, r.learn, false))) {
+    if ((rc = exec_prepare(ctx, &r.P, false, &draw_all)) ||
+        (rc = exec_enqueue(ctx, &r.P, draw_all, G.mran_known, r.learn, kMaxBlindServer))) {
         s->poisoned = true;
         return rc;
     }
-    char* pin = s->pinned + r.pin_off;
-    const size_t rec_b = (size_t)r.shots * (size_t)((r.P.nrec + 7) / 8);
     if (rec_b) SHIP_CHECK(s, hipMemcpyAsync(pin, ctx->packed.p, rec_b, hipMemcpyDeviceToHost, st));
     SHIP_CHECK(s, hipMemcpyAsync(pin + align256(rec_b), ctx->d_err, sizeof(int), hipMemcpyDeviceToHost, st));
     if (r.learn)
