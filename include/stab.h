@@ -297,7 +297,7 @@ int stab_batch_execute(stab_batch *batch, const stab_batch_program *prog, uint8_
  * (STAB_TILE_ONE_BLOCK): the kernel variant with one block of 16 waves per compute unit, else two
  * blocks of 8 waves share one.  0 = the default (8 rows in flight with one x word per lane, 2 with
  * two; lanes sized to the row; one block per compute unit for a batch of no more circuits than the
- * device has compute units, else two).
+ * device has compute units and one of more than 320 qubits among them, else two).
  * The configuration changes speed only: every configuration writes the same records and
  * leaves the same tableaux. */
 #define STAB_TILE_WHOLE_WAVE 0x100

@@ -81,23 +81,28 @@ int batch_layout(int32_t ncirc, const int32_t* n, BatchLayout& L)
         }                                                                                      \
     } while (0)
 
-// Waves a block of a launch over nc circuits: 16 where a compute unit gets at most one circuit
-// anyway (100 shots of a 1249-qubit circuit with T1/T2 noise: 48 ms against 55 ms), 8 where two
-// share it and fill each other's waits (1024 circuits of 64 to 2048 qubits: 20 against 22 ms).
-int batch_waves(int nc, int tile)
+// Waves a block of a launch over nc circuits of at most 64 maxwc qubits, on cus compute units: 16 where
+// a compute unit gets at most one circuit anyway and a circuit has the rows for them, else 8 (two
+// blocks share a compute unit, and a barrier of 8 waves is the shorter).  16 against 8 waves, in ms a
+// launch: 100 shots of a T1/T2 memory of 17 qubits 0.53 and 0.42, of 161 2.8 and 2.4, of 337 5.9 and 5.4
+// (Pauli noise, 200 shots, 1.64 and 1.71), of 449 7.6 and 7.5, of 881 13.6 and 15.7, of 1249 21.6 and
+// 27.1; layered circuits of 1249 qubits, 256 of them 2.2 and 2.8, 257 3.6 and 3.3, 1024 8.4 and 7.7.
+constexpr int kBatchWideWc = 5;
+
+int batch_waves(int nc, int maxwc, int tile, int cus)
 {
     if (tile) return (tile & kTileOneBlock) ? 16 : 8;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 8;
-    return nc <= cus ? 16 : 8;
+    return nc <= cus && maxwc > kBatchWideWc ? 16 : 8;
 }
 
 // The batch kernel over nc circuits of at most 64 maxwc qubits.
 void batch_start(BatchArgs A, int nc, int maxwc, int tile, hipStream_t st)
 {
-    const int bw = batch_waves(nc, tile);
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 0;
+    const int bw = batch_waves(nc, maxwc, tile, cus);
     // what the largest circuit needs, and room for several bands of a pass where that costs no block
     const size_t lds = std::max((size_t)batch_lds_words(maxwc, bw) * 8, (size_t)(bw == 16 ? kLdsBytes : kLdsBytes / 2));
     A.lds_words = (int)(lds / 8);

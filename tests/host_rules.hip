@@ -84,6 +84,17 @@ static void check_captures()
         }
 }
 
+// Waves of the batch kernel: small circuits never take 16, a launch configuration decides itself.
+static void check_batch_waves()
+{
+    for (int nc : {1, 100, 256, 257, 1024})
+        for (int wc : {1, 5, 6, 20, 128}) {
+            const int want = nc <= 256 && wc > 5 ? 16 : 8;
+            EXPECT(batch_waves(nc, wc, 0, 256) == want, "%d circuits of %d words: %d waves", nc, wc, batch_waves(nc, wc, 0, 256));
+            EXPECT(batch_waves(nc, wc, 8, 256) == 8 && batch_waves(nc, wc, 0x208, 256) == 16, "configured: %d, %d", nc, wc);
+        }
+}
+
 int main(int argc, char** argv)
 {
     const struct {
@@ -91,7 +102,8 @@ int main(int argc, char** argv)
         void (*run)();
     } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer},
                   {"list_ahead", check_list_ahead},
-                  {"captures", check_captures}};
+                  {"captures", check_captures},
+                  {"batch_waves", check_batch_waves}};
     for (const auto& c : checks)
         if (argc == 2 && !std::strcmp(argv[1], c.name)) {
             c.run();
