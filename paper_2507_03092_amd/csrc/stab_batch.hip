@@ -1681,8 +1681,10 @@ __global__ void __launch_bounds__(64 * BW) __attribute__((amdgpu_waves_per_eu(4)
                     ext_step = st;
                 }
             }
-            if (ext_step == st) batch_measure_fast<NW, BW>(ap, ci, mi, lp, ev.x, ev.y);
-            else batch_measure_slow<NW, BW>(ap, ci, mi, lp);
+            // (a T1T2 instruction of a small circuit has no event most times: 100 shots of a memory of 17
+            // qubits 421 -> 393 us)
+            if (ext_step != st) batch_measure_slow<NW, BW>(ap, ci, mi, lp);
+            else if (ev.y > 0 || uni(A.meas[mi].kind) != kT1T2K) batch_measure_fast<NW, BW>(ap, ci, mi, lp, ev.x, ev.y);
             ev = make_int2(0, 0);
             ext_step = -1;
             ++st;
