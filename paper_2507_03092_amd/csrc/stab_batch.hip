@@ -188,6 +188,10 @@ constexpr int kMK = 7, kMRK = 8, kRK = 9, kT1T2K = 13;   // kinds (include/stab.
 // A measurement instruction with at least this many targets gets an extraction-only band
 // pass when no gate pass precedes it.
 constexpr int kBatchExtractMin = 8;
+// An instruction on a single target of a circuit of at most so many words takes the slow form, whose
+// steps are fewer (200 circuits of 64 qubits, one target an instruction, 109 us fast and 97 slow; two
+// targets, if they are not random, 109 and 125).
+constexpr int kBatchSlowWc = 4;
 
 __device__ __forceinline__ ulonglong2 batch_key(const BatchArgs& A, int ci)
 {
@@ -1450,6 +1454,35 @@ __device__ BATCH_CALL int batch_window(ArgsPtr ap, int ci_, int mi_, LdsPtr lds_
     return nd;
 }
 
+// The only random-at-start target k of the instruction, on the live tableau (whole block): a window
+// for one is the longer chain of short steps (300 circuits of 64 qubits, a random target a time, 166 ->
+// 152 us; 200 of 1249 qubits 1.62 -> 1.60 ms).
+template <int NW, int BW>
+__device__ BATCH_CALL void batch_single(ArgsPtr ap, int ci_, int mi_, LdsPtr lds_, int k_)
+{
+    BatchArgs A = uniform_args(ap);
+    A.tile = 0;      // (one form of the rowsum: less code)
+    const int ci = uni(ci_), k = uni(k_);
+    const BatchCirc C = uniform_circ(A.circ + ci);
+    const BatchMeas md = uniform_meas(A.meas + uni(mi_));
+    const MeasLds L = meas_lds<BW>(C, (uint64_t*)lds_);
+    const bool stoch = md.kind == kT1T2K;
+    const ulonglong2 key = batch_key(A, ci);
+    uint64_t u0, u1;
+    philox(A.ibase[ci] + md.instr, (uint64_t)k, key.x, key.y, u0, u1);
+    const int o = stoch ? (int)((L.evb[k >> 6] >> (k & 63)) & 1ull) : (int)(u0 >> 63);
+    const int a = A.meas_tg[md.tq + (stoch ? (int)L.sel[k] : k)];
+    MeasWork W;
+    batch_measure_one<NW, BW>(A, C, a, o, L, W);
+    if (threadIdx.x == 0) {
+        if (o) L.outb[k >> 6] |= 1ull << (k & 63);
+        count_add(A.counters, 4, (unsigned long long)W.nrand);
+        count_add(A.counters, 5, (unsigned long long)W.nrows);
+        count_add(A.counters, 6, (unsigned long long)W.bytes);
+    }
+    __syncthreads();
+}
+
 // One M / MR / R / T1T2 instruction of circuit ci.
 //
 // Slow form (any instruction): target by target on the live tableau.  In a T1T2 instruction a Philox
@@ -1502,7 +1535,8 @@ __device__ BATCH_CALL void batch_measure_fast(ArgsPtr ap, int ci_, int mi_, LdsP
         const int nr = batch_list<BW>(L.rndb, 0, KW, -1, -1, rl, L.s_int + 1);
         const bool ran = nr > 0;
         int nd = 0;
-        for (int i = 0; i < nr; i += batch_win(Wc)) nd = uni(batch_window<NW, BW>(ap, ci, mi, lds_, i, nr, nd));
+        if (nr == 1) batch_single<NW, BW>(ap, ci, mi, lds_, rl[0]);
+        else for (int i = 0; i < nr; i += batch_win(Wc)) nd = uni(batch_window<NW, BW>(ap, ci, mi, lds_, i, nr, nd));
         // those and the resets with outcome 1 need columns of the live tableau again: gathered when
         // they are few, else (the tile fits beside what is kept up to 4096 qubits) by a band pass
         if (ran) {
@@ -1658,7 +1692,7 @@ __global__ void __launch_bounds__(64 * BW) __attribute__((amdgpu_waves_per_eu(4)
     // instruction's events (drawn here) or all its targets
     auto columns = [&](const BatchMeas& m) {
         if (!A.cols || !m.fast || C.col_k == 0) return -1;
-        if (m.kind != kT1T2K) return m.K <= C.col_k ? m.K : -1;
+        if (m.kind != kT1T2K) return m.K <= C.col_k && (m.K > 1 || C.Wc > kBatchSlowWc) ? m.K : -1;
         if (C.Wc > 64) return -1;
         ev = batch_events<BW>(A, C, ci, m, L);
         return ev.y <= C.col_k ? ev.y : -1;
