@@ -978,9 +978,11 @@ __device__ int batch_det_from_cols(const BatchArgs& A, const BatchCirc& C, const
     uint64_t xr = 0;
 #pragma unroll
     for (int t = 0; t < NW; ++t) xr |= X[t];
-    const int tot = wave_sum((e & 3) + 2 * (cross & 1)) & 3;
-    xr = wave_or(xr);
-    if (lane == 0 && ((tot & 1) || xr)) atomicOr(A.err, 1);
+    // (without the LDS crossbar: with few rows the reductions are half of it.  300 circuits of 64 qubits,
+    // all measured ten times, none random: 312 -> 292 us)
+    const int tot = wave_sum_uniform((e & 3) + 2 * (cross & 1), lane) & 3;
+    const bool bad = (tot & 1) || __ballot(xr != 0ull);
+    if (lane == 0 && bad) atomicOr(A.err, 1);
     nrows += rows;
     return tot >> 1;
 }
