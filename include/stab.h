@@ -188,7 +188,8 @@ int stab_sample(const stab_instr *instrs, int32_t ninstr, const int32_t *targets
  * caller still provides the tableaux (dev_buf, stab_tableau_bytes bytes) and the host output;
  * every buffer stab_sample would allocate (error flag, counters, the uploaded program, target
  * columns, noise events, window buffers, records) is carved instead from one static device array of
- * STAB_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until the process ends.
+ * STAB_NOALLOC_SCRATCH_BYTES + STAB_NOALLOC_SCRATCH_SLACK that each GPU the library runs on holds
+ * until the process ends; workloads are accepted by the former.
  * Nothing is allocated or freed on the device: no hipMalloc, hipFree, event or stream creation
  * (host-side the stream is compiled in ordinary heap memory, as by stab_sample).  Noise is drawn
  * segment by segment unless the whole program's draws also fit.  Every call on one GPU uses
@@ -197,6 +198,7 @@ int stab_sample(const stab_instr *instrs, int32_t ninstr, const int32_t *targets
  * before the device is touched, when the workload needs more scratch than the array holds
  * (a d=25 surface-code memory experiment with 100 shots needs about 9 MB; d=71 does not fit). */
 #define STAB_NOALLOC_SCRATCH_BYTES (64ull << 20)
+#define STAB_NOALLOC_SCRATCH_SLACK (8ull << 20)
 int stab_sample_noalloc(const stab_instr *instrs, int32_t ninstr, const int32_t *targets,
                         int64_t ntargets, int32_t n, int32_t shots, int32_t mode, uint64_t seed,
                         void *dev_buf, uint64_t buf_bytes, void *hip_stream, uint8_t *out_bits);

@@ -1341,13 +1341,16 @@ int stab_sample(const stab_instr* instrs, int32_t ninstr, const int32_t* targets
 
 // ---------------------------------------------------------------------------------------------
 // stab_sample without device allocation.  Every buffer the library would allocate (error flag,
-// counters, the uploaded program, target columns, noise events, pivot log, records) is carved
+// counters, the uploaded program, target columns, noise events, window buffers, records) is carved
 // from `scratch`, a static device array each GPU holds for the life of the process.  Its name
 // is a host-side stand-in in host code: the device address of each GPU's copy is looked up
 // once per device with hipGetSymbolAddress and only that address is handed to kernels and
 // copies.  Calls on one GPU share the array, so calls that overlap on one GPU race.
 // ---------------------------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[STAB_NOALLOC_SCRATCH_BYTES + (8 << 20)];
+// What is carved may exceed what is counted against the limit (noalloc_bytes) by this much.
+constexpr size_t kScratchSlack = STAB_NOALLOC_SCRATCH_SLACK;
+
+static __device__ __align__(256) unsigned char scratch[STAB_NOALLOC_SCRATCH_BYTES + kScratchSlack];
 
 namespace {
 
@@ -1374,16 +1377,15 @@ int scratch_address(char** out)
     return STAB_OK;
 }
 
-// Scratch bytes stab_sample_noalloc counts against its limit for this program (noise drawn
-// segment by segment).  The random measurements are counted per target of the largest layer (44
-// bytes, a row and its per-shot signs, seven pieces), which bounds what a window of them takes
-// (rand_layout: 48 bytes, a row and signs for at most 64 kWinChunks targets, 16 bytes a copy) to
-// within kScratchSlack.
-constexpr size_t kScratchSlack = 8 << 20;
-
-size_t noalloc_bytes(const Geom& g, const stab_program& P, size_t blob_bytes)
+// Scratch bytes stab_sample_noalloc counts against its limit for this program (noise drawn segment
+// by segment).  The limit is part of the interface, so a gate still counts 8 bytes (it takes 4) and
+// the random measurements count per target of the largest layer (44 bytes, a row and its per-shot
+// signs, seven pieces), which bounds what a window of them takes (rand_layout: 48 bytes, a row and
+// signs for at most 64 kWinChunks targets, 16 bytes a copy) to within kScratchSlack.
+size_t noalloc_bytes(const Geom& g, const stab_program& P, const ProgramBlob& B)
 {
     auto piece = [](size_t b) { return std::max<size_t>(align256(b), 256); };
+    const size_t blob_bytes = B.bytes.size() - (B.noise - B.gates) + piece((size_t)P.ngates * 8);
     size_t total = piece(sizeof(int)) + piece(kNumCounters * kCounterStripes * sizeof(unsigned long long)) +
                    piece(blob_bytes);
     size_t sizes[kExecBufs];
@@ -1413,7 +1415,7 @@ extern "C" int stab_sample_noalloc(const stab_instr* instrs, int32_t ninstr, con
     ProgramBlob B;
     if ((rc = compile_host(g, instrs, ninstr, targets, ntargets, P, B))) return rc;
     if (P.nrec > 0 && !out_bits) return fail(STAB_EINVAL, "out_bits is NULL but the stream records outcomes");
-    const size_t want = noalloc_bytes(g, P, B.bytes.size());
+    const size_t want = noalloc_bytes(g, P, B);
     if (want > (size_t)STAB_NOALLOC_SCRATCH_BYTES)
         return fail(STAB_ERANGE, "stab_sample_noalloc: this workload needs " + std::to_string(want) +
                                      " bytes of scratch; the static scratch holds " +

@@ -95,6 +95,49 @@ static void check_batch_waves()
         }
 }
 
+// The scratch limit of stab_sample_noalloc: a gate counts 8 bytes, and what is carved stays within
+// the slack of what is counted.
+static void check_noalloc_limit()
+{
+    auto counted = [](int n, int shots, int mode, int layers, int K, size_t* carved) {
+        std::vector<stab_instr> ins;
+        std::vector<int32_t> tg;
+        auto add = [&](uint32_t kind, int m) {
+            stab_instr i{};
+            i.kind = kind;
+            i.ntargets = (uint32_t)m;
+            ins.push_back(i);
+            for (int q = 0; q < m; ++q) tg.push_back(q);
+        };
+        for (int l = 0; l < layers; ++l) add(l & 1 ? STAB_S : STAB_H, n);
+        add(STAB_M, K);
+        const Geom g = make_geom(n, shots, mode);
+        stab_program P;
+        ProgramBlob B;
+        if (compile_host(g, ins.data(), (int)ins.size(), tg.data(), (int64_t)tg.size(), P, B)) return (size_t)0;
+        size_t sizes[kExecBufs], sum = 256 + align256(kNumCounters * kCounterStripes * 8) + align256(B.bytes.size());
+        exec_sizes(g, P, false, sizes);
+        for (size_t b : sizes) sum += std::max<size_t>(align256(b), 256);
+        if (carved) *carved = sum;
+        return noalloc_bytes(g, P, B);
+    };
+    for (int n : {32, 64, 4096}) {
+        const size_t a = counted(n, 1, STAB_MODE_SHARED, 32, 1, nullptr), b = counted(n, 1, STAB_MODE_SHARED, 64, 1, nullptr);
+        EXPECT(b - a == 32 * (size_t)(16 + 8 * n), "n %d: 32 layers count %zu bytes", n, b - a);
+    }
+    for (int n : {1, 2, 63, 64, 300, 1249, 4096, 4097, 10240})
+        for (int shots : {1, 2, 100, 1000, 20000, 65535})
+            for (int mode : {STAB_MODE_SHARED, STAB_MODE_FULL})
+                for (int K : {1, 2, 64, 65, 256, 257, 1000, 4000}) {
+                    if (K > n) continue;
+                    size_t carved = 0;
+                    const size_t c = counted(n, shots, mode, 3, K, &carved);
+                    if (c == 0 || c > STAB_NOALLOC_SCRATCH_BYTES) continue;
+                    EXPECT(carved <= STAB_NOALLOC_SCRATCH_BYTES + kScratchSlack, "n %d, %d shots, mode %d, %d targets: %zu carved, %zu counted",
+                           n, shots, mode, K, carved, c);
+                }
+}
+
 int main(int argc, char** argv)
 {
     const struct {
@@ -103,7 +146,8 @@ int main(int argc, char** argv)
     } checks[] = {{"list_by_step", check_list_by_step}, {"windows_of_a_layer", check_windows_of_a_layer},
                   {"list_ahead", check_list_ahead},
                   {"captures", check_captures},
-                  {"batch_waves", check_batch_waves}};
+                  {"batch_waves", check_batch_waves},
+                  {"noalloc_limit", check_noalloc_limit}};
     for (const auto& c : checks)
         if (argc == 2 && !std::strcmp(argv[1], c.name)) {
             c.run();

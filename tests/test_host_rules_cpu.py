@@ -30,7 +30,7 @@ def host_rules(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["list_by_step", "windows_of_a_layer", "list_ahead", "captures", "batch_waves"])
+@pytest.mark.parametrize("check", ["list_by_step", "windows_of_a_layer", "list_ahead", "captures", "batch_waves", "noalloc_limit"])
 def test_host_rule(host_rules, check):
     r = subprocess.run([host_rules, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
