@@ -296,10 +296,10 @@ def surface_summary(r: dict) -> dict:
         "roofline": r["roofline"],
         "rooflines": r["rooflines"],
         "work_per_step": {"random_measurements": int(work[4]), "rowsum_rows": int(work[5]),
-                          "replay_rowsum_rows": int(work[8]), "replay_walked_rows": int(work[9]),
-                          "replay_rows_by_testing": int(work[10]), "replay_events_by_testing": int(work[11]),
+                          "destabilizer_rowsums": int(work[8]), "destabilizer_rows_changed": int(work[9]),
+                          "rows_of_dense_windows": int(work[10]), "events_of_dense_windows": int(work[11]),
                           "deterministic_measurements": int(work[2] + work[6]),
-                          "multiplied_rows": int(work[3]), "chain_rounds": int(work[0]),
+                          "multiplied_rows": int(work[3]), "random_windows": int(work[0]), "dense_windows": int(work[1]),
                           "noise_events": int(work[7])},
     }
 

@@ -291,8 +291,10 @@ void stab_batch_program_destroy(stab_batch_program *prog);
 int stab_batch_execute(stab_batch *batch, const stab_batch_program *prog, uint8_t *out_bits,
                        float *elapsed_ms);
 
-/* Launch configuration of a batch program: the row tile of its rowsum updates.  Bits 0-7:
- * rows each lane group keeps in flight (2, 4 or 8); bit 8 (STAB_TILE_WHOLE_WAVE): every row
+/* Launch configuration of a batch program: how many blocks share a compute unit (bit 9) and, for
+ * instructions that run target by target (repeated qubits, up to 7 targets without a gate or noise
+ * layer before, one target of a small circuit, T1T2 above 4096 qubits), the row tile of a rowsum.  Bits
+ * 0-7: rows each lane group keeps in flight (2, 4 or 8); bit 8 (STAB_TILE_WHOLE_WAVE): every row
  * takes a whole 64-lane wave, else a row takes the smallest power of two of lanes that holds
  * its x words, so one wave updates several rows of a small circuit per load.  With two x
  * words per lane (a circuit above 4096 qubits in the batch) 8 rows in flight run as 4.  Bit 9

@@ -935,7 +935,9 @@ int exec_lds(const Geom& g, int max_lds, ExecLds* out)
 {
     ExecLds E;
     // per-shot sign accumulators in LDS only where they keep two half-band blocks per compute
-    // unit (or where even one block without them would not get two)
+    // unit (or where even one block without them would not get two).  At n = 10081 that is up to 112
+    // shots a copy; four rounds of a d = 71 memory take 4.69 ms with 112, 4.97 with 128, 5.16 with 144
+    // and 5.50 with 176, so leaving LDS costs about 2 %.
     const int seg_base = seg_lds_words(g.Wc) * 4, seg_acc = (seg_lds_words(g.Wc) + g.bpc) * 4;
     E.lds_rd = (seg_acc <= max_lds / 2 || (seg_base > max_lds / 2 && seg_acc <= max_lds)) ? 1 : 0;
     E.seg_lds = (size_t)(seg_lds_words(g.Wc) + (E.lds_rd ? g.bpc : 0)) * 4;

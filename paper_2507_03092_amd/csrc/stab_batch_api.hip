@@ -627,8 +627,8 @@ int stab_batch_autotune(stab_batch* b, stab_batch_program* P, int32_t meas_quota
             return STAB_OK;
         }
     }
-    // candidates: lanes per row sized to the circuit or the whole wave, 2, 4 or 8 rows in
-    // flight, registers capped for two blocks per compute unit or not (one block)
+    // candidates: two blocks of 8 waves per compute unit or one of 16, and for the instructions that run
+    // target by target the lanes of a row, sized to the circuit or the whole wave, and the rows in flight
     std::vector<int> cand;
     for (int one = 0; one < 2; ++one)
         for (int wide = 0; wide < 2; ++wide)

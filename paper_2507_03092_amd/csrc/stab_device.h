@@ -7,7 +7,8 @@ namespace stabdev {
 
 // Most 64-bit column words a lane of the deterministic-measurement wave keeps in registers.
 constexpr int kMaxWordsPerLane = 4;
-// Most 64-row bands of a half: the stabilizer rows k_plan keeps in registers (16 waves of 10).
+// Most 64-row bands of a half: up to it a half-band fits in LDS, and the block's form of k_plan's
+// elimination holds a chunk's words in registers (16 waves of 10).
 constexpr int kMaxBands = 160;
 
 struct Geom {

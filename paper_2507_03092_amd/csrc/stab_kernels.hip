@@ -67,13 +67,6 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m)
     return ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo;
 }
 
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
-{
-    const int lo = __shfl((int)(uint32_t)v, src, 64);
-    const int hi = __shfl((int)(uint32_t)(v >> 32), src, 64);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo;
-}
-
 __device__ __forceinline__ int wave_sum(int v)
 {
 #pragma unroll
@@ -626,7 +619,7 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
 // pass 0, at layer start: the block's eight consecutive targets have their x columns staged in
 // LDS first (a band's eight words are contiguous in Xcol, so the loads are coalesced), then a
 // wave takes each target's column one word per 64-row band and lane.  The first stabilizer with x at the qubit is the pivot: the target is
-// random, its class is that stabilizer index (k_plan and k_apply take it).  Without one the
+// random, its class is that stabilizer index (k_plan takes it for any that is not negative).  Without one the
 // outcome is deterministic: +-Z_a is the product of the stabilizers NR + i over the
 // destabilizers i with x at the qubit (class -1).  pass 1, after the random targets on the final
 // tableau (only when one ran): the targets k_plan marked deterministic (-2)
@@ -671,10 +664,10 @@ k_det(Geom g, const uint64_t* __restrict__ tab, const uint64_t* __restrict__ rs,
         s_rows = 0;
     }
     if (pass == 0) {
-        // the next launch (k_plan) sets this when a random target runs
+        // k_plan counts its windows here
         if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ran = 0;
     } else {
-        // (ran_log, when given: whether a target of this layer ran, for the host)
+        // (ran_log, when given: how many windows of random targets this layer took, for the host)
         const int r = *ran;
         if (ran_log && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ran_log = r;
         if (r == 0) return;
