@@ -652,7 +652,6 @@ int create_ctx(int32_t n, int32_t shots, int32_t mode, uint64_t seed, uint64_t f
     for (int lrd = 0; lrd < 2; ++lrd)
         for (int q : {1, 64 * kMaxBands})
             (void)hipFuncSetAttribute((const void*)segment_kernel(q, lrd), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
     (void)hipFuncSetAttribute((const void*)k_plan<false>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds_bytes(64 * kMaxBands));
     (void)hipFuncSetAttribute((const void*)k_det<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipFuncSetAttribute((const void*)k_det<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1080,6 +1079,8 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
             const Snap snap{ctx->tab, ctx->rs, ctx->rd, obuf, ctx->seed, ctx->first_shot, base + m.instr, m.pos_base,
                       g.bpc <= 64 && std::min(R.Tc, K2) <= kFusedSnaps};
             uint64_t* post = ask ? ctx->post : nullptr;
+            if (post)
+                (void)hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds);
             for (int w = 0; w < nwin; ++w) {
                 if (w == until) {
                     // many windows that may all be empty: ask how many targets are left
