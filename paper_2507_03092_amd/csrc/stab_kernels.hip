@@ -307,6 +307,8 @@ struct ItemBuf {
 // then be waited for with it).
 __device__ __forceinline__ void landed(uint2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 
+constexpr int kSegThreads = 1024;   // of a block of k_segment
+
 // Bytes of a list of `entries` that the descriptor of its first `ahead` covers (the whole list's would
 // not fit 32 bits from 2^29 entries on).
 __host__ __device__ constexpr int ahead_bytes(int entries, int ahead) { return (entries < ahead ? entries : ahead) * 8; }
@@ -321,7 +323,7 @@ __device__ __forceinline__ void fetch_item(const SegArgs& a, int4 d, int tid, in
     b.z = uni(d.z);
     b.w = uni(d.w);
     const void* list = b.noise() ? (const void*)(a.events + b.y) : (const void*)(a.gates + b.y);
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)list, (short)0, ahead_bytes(b.entries(), PF * nt), 0x00027000);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)list, (short)0, ahead_bytes(b.entries(), PF * kSegThreads), 0x00027000);
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
         const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (tid + u * nt) * 8, 0, 0);
@@ -470,7 +472,7 @@ __device__ __forceinline__ bool any_bit(const uint32_t (&w)[16])
 // d = 25 95 -> 86 us.
 // ------------------------------------------------------------------------------------------
 template <bool LRD, int PF>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(8)))
 k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
           uint64_t* __restrict__ rd, SegArgs a)
 {
@@ -479,7 +481,8 @@ k_segment(Geom g, uint64_t* __restrict__ tab, uint64_t* __restrict__ rs,
     const int hb = blk_x(g);                     // half-band: band = hb >> 1, half = hb & 1
     const int band = hb >> 1, half = hb & 1;
     const int s = blk_y(g);
-    const int tid = threadIdx.x, nt = blockDim.x;
+    constexpr int nt = kSegThreads;
+    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = uni(tid >> 6), nwaves = nt >> 6;
     const int RS = g.RS, Wc = g.Wc, RP = seg_pairs(Wc);
     uint2* T = (uint2*)lds32;                    // 64 x RP pairs
