@@ -953,16 +953,16 @@ constexpr int kFusedSnaps = 32;
 constexpr int kMaxBlindWindows = 4, kMaxBlindServer = 16;
 
 // The pending targets left by the last launched window, from the word that k_plan answers in or,
-// without one (the context allocates nothing), from the window's descriptor on the device.  Reading
-// back idles the device for 32 to 36 us a layer: 30 rounds of a d = 33 memory that goes on from
-// another state take 3.12 ms that way and 2.15 ms with the word, a first execution at d = 45 5.32 and
-// 3.72 ms (2.66 and 4.90 with the targets one after another in one launch).
+// without one (the context allocates nothing), from the window's descriptor on the device.  Either
+// idles the device for a while: a d = 33 memory takes 4.88 ms with an asynchronous copy and a wait for
+// the stream in each of its layers, 4.03 with one blocking copy and 3.87 with the word (4.38 with the
+// targets one after another in one launch); a first execution at d = 45 5.32 ms with the copy and the
+// wait, 3.72 with the word.
 int windows_left(stab_ctx* ctx, const RandBufs& R, int* left)
 {
     if (!ctx->post) {
         int v[4] = {0, 0, 0, 0};   // the first copy's (the same in all)
-        HIP_CHECK(ctx, hipMemcpyAsync(v, R.win, 16, hipMemcpyDeviceToHost, ctx->stream));
-        HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
+        HIP_CHECK(ctx, hipMemcpyWithStream(v, R.win, 16, hipMemcpyDeviceToHost, ctx->stream));
         *left = v[0] - v[1] - (v[2] & ~kDenseFlag);
         return STAB_OK;
     }
