@@ -234,8 +234,8 @@ int stab_set_timing(stab_ctx *ctx, int32_t kernel_mask);
  * as at capture (a program executed right after stab_reset, again and again, replays); any
  * other execution captures anew, or runs eagerly where it starts away from |0...0> and a layer
  * measures more than 256 qubits (64 above 4096 qubits).  Results are those of the eager launches.
- * The record copy to the host and the consistency check stay outside the graph.  Errors: STAB_EINVAL (null
- * context). */
+ * The record copy to the host and the consistency check stay outside the graph.  Errors:
+ * STAB_EINVAL (null context). */
 int stab_set_graph(stab_ctx *ctx, int32_t enable);
 int stab_get_kernel_times(stab_ctx *ctx, double *ms, uint64_t *launches, int32_t nkernels);
 
@@ -418,8 +418,8 @@ int stab_server_submit(stab_server *server, int32_t prog, int32_t shots, uint64_
                        int64_t *id_out);
 
 /* Retire shared-lane requests that completed, admit what fits (shared-lane requests start at
- * once, or when the first of their stream has finished), run one batch-lane launch over every resident batch-lane shot and retire the batch-lane
- * requests that finished (their records are copied to host memory and their bytes freed).  Waits
+ * once, or when the first of their stream has finished), run one batch-lane launch over every
+ * resident batch-lane shot and retire the batch-lane requests that finished (their records are copied to host memory and their bytes freed).  Waits
  * for the batch launch, and when a program of more than 4096 qubits with a layer of more than 1024
  * targets runs in the shared lane for the first time, for the counts of its layers' random targets.
  * *finished_out (may be NULL) receives the number of requests that finished. */

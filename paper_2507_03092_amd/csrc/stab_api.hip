@@ -1079,7 +1079,8 @@ int exec_enqueue(stab_ctx* ctx, stab_program* P, bool draw_all, bool use_mran, b
                       g.bpc <= 64 && std::min(R.Tc, K2) <= kFusedSnaps};
             uint64_t* post = ask ? ctx->post : nullptr;
             if (post)
-                (void)hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, plan_lds);
+                (void)hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          plan_lds_bytes(64 * kMaxBands));
             for (int w = 0; w < nwin; ++w) {
                 if (w == until) {
                     // many windows that may all be empty: ask how many targets are left

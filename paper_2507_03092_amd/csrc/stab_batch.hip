@@ -284,7 +284,7 @@ __host__ __device__ __forceinline__ void list_by_step(int nsteps, int tid, int* 
 // are left alone.
 template <int BW>
 __device__ BATCH_CALL void batch_segment(ArgsPtr ap, int ci_, int st_, int en_, LdsPtr lds_, int tq_, LdsPtr sel_,
-                                           int ncol_)
+                                         int ncol_)
 {
     constexpr int nt = (64 * BW), PF = 4;      // 16-byte pairs a thread loads ahead
     const BatchArgs A = uniform_args(ap);
@@ -979,7 +979,7 @@ __device__ int batch_det_from_cols(const BatchArgs& A, const BatchCirc& C, const
 #pragma unroll
     for (int t = 0; t < NW; ++t) xr |= X[t];
     // (without the LDS crossbar: with few rows the reductions are half of it.  300 circuits of 64 qubits,
-    // all measured ten times, none random: 312 -> 292 us)
+    // all measured ten times, none random: 312 -> 296 us)
     const int tot = wave_sum_uniform((e & 3) + 2 * (cross & 1), lane) & 3;
     const bool bad = (tot & 1) || __ballot(xr != 0ull);
     if (lane == 0 && bad) atomicOr(A.err, 1);
