@@ -419,10 +419,11 @@ int stab_server_submit(stab_server *server, int32_t prog, int32_t shots, uint64_
 
 /* Retire shared-lane requests that completed, admit what fits (shared-lane requests start at
  * once, or when the first of their stream has finished), run one batch-lane launch over every
- * resident batch-lane shot and retire the batch-lane requests that finished (their records are copied to host memory and their bytes freed).  Waits
- * for the batch launch, and when a program of more than 4096 qubits with a layer of more than 1024
- * targets runs in the shared lane for the first time, for the counts of its layers' random targets.
- * *finished_out (may be NULL) receives the number of requests that finished. */
+ * resident batch-lane shot and retire the batch-lane requests that finished (their records are
+ * copied to host memory and their bytes freed).  Waits for the batch launch, and when a program of
+ * more than 4096 qubits with a layer of more than 1024 targets runs in the shared lane for the
+ * first time, for the counts of its layers' random targets.  *finished_out (may be NULL) receives
+ * the number of requests that finished. */
 int stab_server_step(stab_server *server, int32_t *finished_out);
 
 /* Drop a request: queued, resident (a shared-lane request's launches finish; its bytes are freed
